@@ -230,8 +230,8 @@ ll_status ll_plan_stack_bytes(const ll_plan* plan, int64_t* device_bytes,
  * work-groups per loop launch, hidden units per work-group (the cell units
  * of a work-group in the chip-wide form), row groups (independent
  * recurrences), the loop form (LL_LOOPS_*: XCD-local where one XCD holds the
- * recurrent weights, chip-wide where it cannot (bf16 H = 2048, f32
- * H = 1024, B <= 256), grid-barrier otherwise), and whether a two-layer plan runs its layers
+ * recurrent weights, chip-wide where it cannot (bf16 H <= 2048, f32
+ * H <= 1024, B <= 256), grid-barrier otherwise), and whether a two-layer plan runs its layers
  * as a wavefront (1: one launch per direction runs both layers, the upper
  * layer's step t beside the lower layer's step t+1 (forward) or t-1
  * (gradient); 0: one launch per layer).  Any output may be NULL.

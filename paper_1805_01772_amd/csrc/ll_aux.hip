@@ -311,11 +311,12 @@ __global__ __launch_bounds__(256) void convert_kernel(const float* __restrict__ 
 // c < C, 64 x 64 elements in 16-byte chunks both ways: thread (row, chunk)
 // loads KPC consecutive columns of one input row into LDS (row pitch padded
 // by one chunk), thread (column, chunk) stores KPC consecutive rows of one
-// output row.  R, C, ldi and ldo are multiples of KPC and both arrays
+// output row (row 4 u + g for column c = g um + u when um > 0: unit-major
+// gates).  R, C, ldi and ldo are multiples of KPC and both arrays
 // 16-byte aligned (the plan checks I and H; W and W^T are 16-byte aligned).
 template <typename T>
 __device__ void transpose_tile(const T* __restrict__ in, int R, int C, int ldi, T* __restrict__ out,
-                               int ldo, int r0, int c0, T (*tile)[64 + Op<T>::kPerChunk]) {
+                               int ldo, int r0, int c0, int um, T (*tile)[64 + Op<T>::kPerChunk]) {
   constexpr int KPC = Op<T>::kPerChunk;
   constexpr int CPR = 64 / KPC;
   for (int idx = threadIdx.x; idx < 64 * CPR; idx += blockDim.x) {
@@ -338,7 +339,7 @@ __device__ void transpose_tile(const T* __restrict__ in, int R, int C, int ldi, 
       for (int e = 0; e < KPC; ++e) tmp[e] = tile[j * KPC + e][cl];
       uint4 v;
       __builtin_memcpy(&v, tmp, 16);
-      *reinterpret_cast<uint4*>(out + (long)c * ldo + r) = v;
+      *reinterpret_cast<uint4*>(out + (long)(um ? 4 * (c % um) + c / um : c) * ldo + r) = v;
     }
   }
   __syncthreads();   // the tile is free for the next one
@@ -361,7 +362,7 @@ __global__ __launch_bounds__(512) void fwd_setup_kernel(FwdSetupArgs a) {
     const int kk = k - (j ? a.job[0].tiles : 0);
     const int tr = kk / q.tiles_c, tc = kk - tr * q.tiles_c;
     transpose_tile<T>(static_cast<const T*>(q.in), q.R, q.C, q.ldi, static_cast<T*>(q.out), q.ldo, tr * 64,
-                      tc * 64, tile);
+                      tc * 64, q.um, tile);
   }
 }
 
@@ -409,7 +410,7 @@ __global__ __launch_bounds__(256) void small_tasks_kernel(SmallTasks ts) {
 template <typename T>
 hipError_t launch_fwd_setup(const int* seq_len, int B, int T_max, int* perm, int* active, int* off,
                             int* rowmap, int* meta, int* trip_out, int nw, const T* const* W, const int* R,
-                            int C, T* const* WT, hipStream_t s) {
+                            int C, int um, T* const* WT, hipStream_t s) {
   if (nw < 0 || nw > 2) return hipErrorInvalidValue;
   FwdSetupArgs a{};
   int n_pow2 = 1;
@@ -430,6 +431,7 @@ hipError_t launch_fwd_setup(const int* seq_len, int B, int T_max, int* perm, int
     q.C = C;
     q.ldi = C;
     q.ldo = R[l];
+    q.um = um;
     q.tiles_c = (C + 63) / 64;
     q.tiles = ((R[l] + 63) / 64) * q.tiles_c;
     tiles += q.tiles;
@@ -652,9 +654,9 @@ hipError_t launch_convert(const float* in, long n, T* out, hipStream_t s) {
 }
 
 template hipError_t launch_fwd_setup<float>(const int*, int, int, int*, int*, int*, int*, int*, int*, int,
-                                             const float* const*, const int*, int, float* const*, hipStream_t);
+                                             const float* const*, const int*, int, int, float* const*, hipStream_t);
 template hipError_t launch_fwd_setup<bf16_t>(const int*, int, int, int*, int*, int*, int*, int*, int*, int,
-                                              const bf16_t* const*, const int*, int, bf16_t* const*, hipStream_t);
+                                              const bf16_t* const*, const int*, int, int, bf16_t* const*, hipStream_t);
 template <typename T>
 __global__ __launch_bounds__(256) void pre_jobs_kernel(PreJobs j) {
   pre_jobs_body<T>(j, blockIdx.x, gridDim.x, 256);

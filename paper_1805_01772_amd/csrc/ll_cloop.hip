@@ -1,75 +1,109 @@
 // Chip-wide variants of the two device-side loops, for shapes whose
-// recurrent weights need more than one XCD (bf16 H = 2048: W_h is 32 MB; f32
-// H = 1024: 16 MB).  The weights stay in registers for the whole loop, split
-// over all 256 work-groups, and the loop state crosses XCDs every step.
+// recurrent weights need more than one XCD (bf16 H in (1024, 2048], f32 H in
+// (512, 1024], at most 256 sequences).  The weights stay in LDS for the whole
+// loop, split over the work-groups of the chip, and the loop state crosses
+// XCDs every step.
 //
-// Work split.  XCD x owns hidden units [x UX, (x+1) UX), UX = H / 8.  Its 32
-// work-groups form a KG x NG grid (rank = kq NG + nq): work-group (kq, nq)
-// holds the weights of reduction slice kq (KC = H / 2 rows of the product's
-// reduction dimension) for the output columns of N-group nq, and runs the
-// cell of CW units of that N-group (the N-group's units split KG ways).
-//   forward:  z = h_{t-1} W_h, K = H, KG = 2, NG = 16; N-group columns are
-//             the 4 gates of UN = 4 NCT units.
-//   gradient: dh_{t-1} = dz_t W_h^T, K = 4H, KG = 8, NG = 4; N-group
-//             columns are UN = 16 NCT units.
-// Both give every work-group KC x 16 NCT weights (KSW k-steps per wave, the
-// K slice split over 8 waves) and CW = 2 NCT cell units.  Every row tile of
-// the batch runs on every work-group.
+// Work split.  The output columns of the recurrent product are cut into
+// groups of 64 (forward: the four gates of 16 units; gradient: 64 units) and
+// the reduction into KG slices; work-group (group, slice) holds a slice of H/32
+// k-steps x 64 columns (64 H bytes of LDS) and runs the cell of CW of the
+// group's units.  A group's KG work-groups sit on one XCD.
+//   forward:  z = h_{t-1} W_h, K = H,  KG = 2 (bf16) / 4 (f32)
+//   gradient: dh_{t-1} = dz_t W_h^T, K = 4H, KG = 8 / 16
 //
-// One step (forward; the gradient loop is the same with its cell first):
-//   phase A: for every running row tile, wait until the producers of the
-//     wave's k-steps of h_{t-1} have published them, load them from the
-//     exchange ring (device-scope loads, two tiles ahead), multiply, reduce
-//     the 8 waves' partials in LDS (two buffers, one barrier per tile) and
-//     store the work-group's partial product (16 rows x 16 NCT columns);
-//     then publish all tiles' partials at once.
-//   phase B: wait for the KG partial products of the own N-group, sum them,
-//     add the input projection, run the cell for CW units of every row, store
-//     h_t into the ring with device-scope stores (written through to where
-//     every XCD's loads see it), publish; then the h history, stack and y.
-// Ring slots (two per row tile) and partial slots (two) are reused two steps
-// later; every writer of a slot has, through the chain of flags it waited
-// for, seen every reader of the slot's previous contents finish.  Every wait
-// has the loop's wall-clock limit and abort flag.
+// Inside a work-group every wave runs the recurrence of its own rows alone:
+// the batch is cut into groups of 32 rows, wave w takes row group w % RW and
+// share w / RW of the work-group's reduction slice (RW KW = 8: KW = 1 for
+// more than 128 rows, 2 for more than 64, else 4, so that a small batch still
+// spreads over the waves).  No barrier and no sum over waves stands in
+// a step: the shares meet as partial products of the group, like the KG
+// slices, and the waves of a SIMD hide each other's waits.  (The form this
+// replaced kept the weights in registers, split the reduction over the eight
+// waves of a work-group, and so summed eight partials through LDS behind a
+// barrier for every 16 rows; it took only H = 2048 / 1024, other widths ran on
+// the grid-barrier loops.  Training step, before and after: two layers of bf16
+// H = 2048 at B = 256 19.5 -> 17.7 ms; bf16 H = 1536, B = 72, 90 steps 6.2 ->
+// 1.9 ms; f32 H = 640 inference, B = 50, 73 steps 1.53 -> 1.00 ms.)
+//
+// One step of a wave (forward; the gradient loop runs its cell first):
+//   phase A: wait for the producers of its k-steps of h_{t-1}, stream them
+//     from the exchange ring (device-scope loads, 8 to 16 k-steps in flight)
+//     against the weights in LDS (32x32 MFMAs), store the 32 x 64 partial
+//     product into the XCD's L2 and set the wave's partial flag;
+//   phase B: wait for the KG KW partial products of its column group, sum
+//     them for its share of the cells, add the input projection, run the
+//     cell, store h_t into the ring with device-scope stores (written through
+//     to where every XCD's loads see it), set the wave's exchange flag; then
+//     the h history, stack and y.
+//
+// What is reused when.  Ring slot t % 2 is rewritten at step t + 2 by a wave
+// that has waited for every partial of its group at step t + 2 (t - 2): the
+// waves behind them have waited for the exchange flags of step t + 1 of, taken
+// together, every producer of the row group, each set after its wave read
+// slot t % 2.  There is one partial slot: a wave stores its partial of step
+// t only after every wave of its column group has set its exchange flag of
+// step t - 1 (gradient: of step t), which follows the reads of the previous
+// partial.  Every wait has the loop's wall-clock limit and abort flag.
+//
+// Exchange blocks are 1 KB, one k-step (16 bf16 or 8 f32 columns) of 32 rows
+// in the matrix cores' operand order: lane l holds row l % 32, 16-byte chunk
+// l / 32.  The reduction runs over units forward and over 4 unit + gate in the
+// gradient, so a unit's four dz values are adjacent.  W^T rows, the input
+// projection's columns and the stack's gate values are in the same
+// 4 unit + gate order: one 16-byte access per row and unit.
+//
+// Bound at bf16 H = 2048, B = 256, per step and compute unit: 512 KB of
+// exchange blocks from the L2 (4.3 us at the measured 50 B/clk), 1 MB of LDS
+// weight reads (3.4 us at 128 B/clk) beside 33.5 MFLOP (3.4 us).
+#include <type_traits>
+
 #include "ll_kernels.h"
 #include "ll_exchange.h"
 
 namespace ll {
 
-constexpr int CNW = 8;
-constexpr int CNT = 64 * CNW;
-constexpr int CWIN = 256;    // steps of loop metadata kept in LDS
-
-template <typename T, int KSW, int NCT>
-struct CShape {
-  static constexpr int KPC = Op<T>::kPerChunk;
-  static constexpr int H = 64 * KSW * KPC;
-  static constexpr int UX = H / 8;         // units per XCD
-  static constexpr int KC = H / 2;         // reduction slice per work-group (both loops)
-  static constexpr int CW = 2 * NCT;       // cell units per work-group
-  static constexpr int CT = 16 * CW;       // cell threads per row tile
-  static constexpr int TPP = CNT / CT;     // row tiles per cell pass
-  static constexpr int PW = 16 * 16 * NCT; // partial floats per (work-group, row tile)
-  static constexpr int RB = CNW * NCT * 256;  // floats of one LDS partial buffer
-  static constexpr int EPT = NCT / 2;          // partial floats each thread reduces
-  static_assert(EPT == 1 || EPT == 2, "reduction split");
-  static constexpr int NPROD = KSW * 4 * KPC / CW;   // producers of one wave's k-steps
-  static_assert(KSW * KPC == 8 * NCT, "H = 64 KSW KPC = 512 NCT");
-  static_assert(CW % KPC == 0 && CT % 64 == 0 && TPP * CT == CNT, "cell layout");
-  static_assert(NPROD <= 64, "one lane per producer");
-};
-
 namespace {
 
-__device__ __forceinline__ void c_window(const CLoopArgs& a, int* win, int lo) {
-  __syncthreads();
-  for (int i = threadIdx.x; i <= CWIN; i += blockDim.x) {
-    const int t = lo + i;
-    win[i] = (t >= 0 && t <= a.T_max) ? a.active[t] : 0;
-    win[CWIN + 1 + i] = (t >= 0 && t <= a.T_max) ? a.off[t] : 0;
-  }
-  __syncthreads();
+constexpr int CNW = 8;
+constexpr int CNT = 64 * CNW;
+constexpr int kPartFloats = 32 * 64;   // a wave's partial product
+constexpr int kScratch = 2048;         // LDS bytes of a wave's layout changes
+
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+
+// One k-step: every lane supplies a 16-byte chunk of A and of B (f32: four
+// 32x32x2 MFMAs; element j of the lane's chunk is its k-slot in the j-th).
+template <typename T>
+__device__ __forceinline__ f32x16 mfma32(uint4 a, uint4 b, f32x16 c);
+template <>
+__device__ __forceinline__ f32x16 mfma32<bf16_t>(uint4 a, uint4 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
+                                                c, 0, 0, 0);
 }
+template <>
+__device__ __forceinline__ f32x16 mfma32<float>(uint4 a, uint4 b, f32x16 c) {
+  c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
+  return c;
+}
+
+// KG: reduction slices; KW: waves that share a slice.
+template <typename T, int KG_, int KW_>
+struct CShape {
+  static constexpr int KPC = Op<T>::kPerChunk;
+  static constexpr int KG = KG_, KW = KW_;
+  static constexpr int NGX = 32 / KG;          // column groups per XCD
+  static constexpr int CW = KPC;               // cell units per work-group: one 16-byte chunk
+  static constexpr int RW = CNW / KW;          // row groups
+  static constexpr int RPK = 32 / KW;          // rows of a wave's cells
+  static constexpr int RPL = CW * RPK > 64 ? CW * RPK / 64 : 1;   // rows per lane
+  static constexpr int NP = KG * KW;           // partials of a column group
+  static_assert(RPL == 1 || RPL == 2 || RPL == 4, "rows per lane");
+  static_assert(NP <= 64, "one lane per partial flag");
+};
 
 __device__ __forceinline__ void c_fail(const CLoopArgs& a) {
   if (threadIdx.x == 0) {
@@ -78,40 +112,19 @@ __device__ __forceinline__ void c_fail(const CLoopArgs& a) {
   }
 }
 
-// Work-group (0..255 over the chip) of the cell that produces unit j, for a
-// KG x NG split with NG-group width UN and cell width CW.
-template <int UX, int UN, int CW, int NG>
-__device__ __forceinline__ int producer_of(int j) {
-  const int v = j % UX;
-  return (j / UX) * 32 + ((v % UN) / CW) * NG + v / UN;
-}
-
-// Wait until every flag this lane names is >= need: flag (tile m, producer
-// pr) for the pairs i = lane + 64 j < n_pairs, m = i / NPROD, pr = i % NPROD;
-// flag index m * 256 + prod[pr] where prod is the lane's producer table.
-template <int NPROD, int NJ>
-__device__ __forceinline__ void wait_tiles(const CLoopArgs& a, const unsigned* flags, int nt, int my_prod,
-                                           unsigned need) {
+// Wait until flags[0 .. n) are all >= need, 64 at a time.
+__device__ __forceinline__ void wait_range(const CLoopArgs& a, const unsigned* flags, int n, unsigned need) {
   const int lane = threadIdx.x & 63;
-  const unsigned* fp[NJ];
-  bool mine[NJ];
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    const int i = lane + 64 * j;
-    const int m = i / NPROD, pr = i % NPROD;
-    // the producer of pair i is the one lane pr names
-    const int id = __shfl(my_prod, pr, 64);
-    mine[j] = m < nt;
-    fp[j] = flags + (mine[j] ? m * 256 + id : 0);
-  }
   unsigned long long t0 = 0;
   unsigned polls = 0;
-  while (true) {
-    bool pend = false;
-#pragma unroll
-    for (int j = 0; j < NJ; ++j)
-      pend |= mine[j] && __hip_atomic_load(fp[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need;
-    if (__builtin_amdgcn_ballot_w64(pend) == 0) return;
+  for (int i0 = 0; i0 < n;) {
+    const bool mine = i0 + lane < n;
+    const unsigned f =
+        __hip_atomic_load(flags + (mine ? i0 + lane : 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__builtin_amdgcn_ballot_w64(mine && f < need) == 0) {
+      i0 += 64;
+      continue;
+    }
     if (polls == 0) t0 = wall_clock64();
     __builtin_amdgcn_s_sleep(1);
     if ((++polls & 255u) == 0) {
@@ -125,35 +138,114 @@ __device__ __forceinline__ void wait_tiles(const CLoopArgs& a, const unsigned* f
   }
 }
 
-// The 8 waves' partial products of one row tile, summed: thread tid takes
-// EPT of the 4 rows of item (column tile, lane) it = tid / (4 / EPT), the
-// LDS buffer being [wave][item] float4.  out(c, rq, e, v) receives column
-// c = ct*16 + lane % 16, row 4 rq + e.
-template <int NCT, int EPT, typename Out>
-__device__ __forceinline__ void reduce_waves(const float4* rb, Out out) {
-  const int tid = threadIdx.x;
-  const int it = tid / (4 / EPT), e0 = (tid % (4 / EPT)) * EPT;
-  const float* rf = reinterpret_cast<const float*>(rb) + it * 4 + e0;
-  float v[EPT];
-#pragma unroll
-  for (int i = 0; i < EPT; ++i) v[i] = rf[i];
-#pragma unroll
-  for (int w2 = 1; w2 < CNW; ++w2)
-#pragma unroll
-    for (int i = 0; i < EPT; ++i) v[i] += rf[w2 * NCT * 256 + i];
-  const int c = (it >> 6) * 16 + (it & 15), rq = (it >> 4) & 3;
-#pragma unroll
-  for (int i = 0; i < EPT; ++i) out(c, rq, e0 + i, v[i]);
+// LDS layout changes within one wave: its earlier LDS writes are ordered
+// before its later reads (the hardware runs a wave's LDS operations in
+// order; the fence keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
-// Byte offset of element (row, column n) of row tile m in ring slot sl:
-// blocks of 4 KPC columns, lane l of a block holding row l % 16, columns
-// (l / 16) KPC .. + KPC.
+__device__ __forceinline__ void st16_dev(__amdgpu_buffer_rsrc_t r, unsigned off, uint4 v) {
+  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+  __builtin_amdgcn_raw_buffer_store_b128(u32x4{v.x, v.y, v.z, v.w}, r, off, 0, kCpolStoreDev);
+}
+
+// k-steps of a wave's loop body and so of its loads in flight: a share is
+// padded to whole bodies (with zero weights, and zeros for ring blocks).
 template <typename T>
-__device__ __forceinline__ unsigned ring_off(int sl, int mrt, int ks_tile, int m, int row, int n) {
-  constexpr int KPC = Op<T>::kPerChunk;
-  const int ks = n / (4 * KPC), cq = (n % (4 * KPC)) / KPC, e = n % KPC;
-  return (unsigned)(((((sl * mrt + m) * ks_tile + ks) * 64 + cq * 16 + row) * 16) + e * (int)sizeof(T));
+constexpr int c_unroll() { return sizeof(T) == 2 ? 8 : 4; }
+template <typename T>
+__host__ __device__ constexpr int c_share(int KS, int KW) {   // padded k-steps of a share of the slice
+  const int n = (KS + KW - 1) / KW;
+  return (n + c_unroll<T>() - 1) / c_unroll<T>() * c_unroll<T>();
+}
+
+// The wave's partial product: acc[ct] += ring blocks (rs, 1 KB each, zeros
+// past the range) times the weight k-steps [0, U ng) in LDS (two column tiles
+// of 1 KB each), in groups of U from group `rot` on, around: the work-groups
+// of an XCD all read the same freshly written blocks, and each starts
+// elsewhere so that they do not all wait for the same misses.  A block's
+// registers are refilled as soon as its products are issued, and the weights
+// come from LDS two k-steps ahead (left to the compiler, every pair of
+// products waited for its own LDS reads: 218 clocks a k-step instead of 64).
+// `behind` runs once the last blocks have been asked for.
+template <typename T, typename Behind>
+__device__ __forceinline__ void c_product(__amdgpu_buffer_rsrc_t rs, const uint4* w, int ng, int rot,
+                                          f32x16 (&acc)[2], Behind behind) {
+  constexpr int U = c_unroll<T>();
+  const int lane = threadIdx.x & 63;
+  uint4 b[U], wv[2][4];
+  const uint4* wl = w + lane;
+  auto rd = [&](uint4 (&v)[4], int g, int c) {   // weights of k-steps 2c, 2c + 1 of group g
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = wl[(g * U + 2 * c) * 128 + i * 64];
+  };
+  int cur = rot % ng;
+#pragma unroll
+  for (int i = 0; i < U; ++i) b[i] = ld_chunk_l2(rs, (unsigned)(((cur * U + i) << 10) + lane * 16));
+  rd(wv[0], cur, 0);
+  for (int left = ng; left > 0; --left) {
+    const int nxt = cur + 1 < ng ? cur + 1 : 0;
+    if (left == 1) behind();
+#pragma unroll
+    for (int c = 0; c < U / 2; ++c) {
+      rd(wv[(c + 1) & 1], c + 1 < U / 2 ? cur : nxt, c + 1 < U / 2 ? c + 1 : 0);
+      __builtin_amdgcn_sched_barrier(0);
+      const uint4(&v)[4] = wv[c & 1];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        acc[0] = mfma32<T>(b[2 * c + k], v[2 * k], acc[0]);
+        acc[1] = mfma32<T>(b[2 * c + k], v[2 * k + 1], acc[1]);
+        // (the last group asks past the range: no traffic)
+        b[2 * c + k] = ld_chunk_l2(rs, left > 1 ? (unsigned)(((nxt * U + 2 * c + k) << 10) + lane * 16) : kOOB);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    cur = nxt;
+  }
+}
+
+// Partial product of a wave to memory: element (column c, row r) at float
+// ((((c/32) 4 + r/8) 32 + c%32) 2 + (r/4)%2) 4 + r%4, the result registers'
+// own order, so that each store instruction writes 1 KB in one piece.
+__device__ __forceinline__ unsigned part_off(int c, int r) {
+  return (unsigned)((((((c >> 5) * 4 + (r >> 3)) * 32 + (c & 31)) * 2 + ((r >> 2) & 1)) * 4 + (r & 3)) * 4);
+}
+__device__ __forceinline__ void store_partial(float* p, const f32x16 (&acc)[2]) {
+  const int lane = threadIdx.x & 63, l32 = lane & 31, hf = lane >> 5;
+  float4* p4 = reinterpret_cast<float4*>(p);
+#pragma unroll
+  for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      p4[((ct * 4 + q) * 32 + l32) * 2 + hf] =
+          make_float4(acc[ct][4 * q], acc[ct][4 * q + 1], acc[ct][4 * q + 2], acc[ct][4 * q + 3]);
+}
+// RPL consecutive rows of one column of a partial.
+template <int RPL>
+__device__ __forceinline__ void load_partial(__amdgpu_buffer_rsrc_t r, unsigned off, float (&v)[RPL]) {
+  if constexpr (RPL == 4) {
+    const uint4 u = ld_chunk_l2(r, off);
+    v[0] = __uint_as_float(u.x);
+    v[1] = __uint_as_float(u.y);
+    v[2] = __uint_as_float(u.z);
+    v[3] = __uint_as_float(u.w);
+  } else if constexpr (RPL == 2) {
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    const u32x2 u = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, kCpolSc1));
+    v[0] = __uint_as_float(u.x);
+    v[1] = __uint_as_float(u.y);
+  } else {
+    v[0] = ld_f32_l2(r, off);
+  }
+}
+
+// Length of the row group's longest row (its first: rows are in length
+// order), capped at the trip count (0 when the lengths failed the range check).
+__device__ __forceinline__ int group_len(const CLoopArgs& a, int rg, int T_eff) {
+  if (rg * 32 >= a.B || T_eff <= 0) return 0;
+  return uni(min(T_eff, a.seq_len[a.perm[rg * 32]]));
 }
 
 }  // namespace
@@ -161,510 +253,532 @@ __device__ __forceinline__ unsigned ring_off(int sl, int mrt, int ks_tile, int m
 // ---------------------------------------------------------------------------
 // Forward loop, chip-wide.
 // ---------------------------------------------------------------------------
-template <typename T, int KSW, int NCT, int MRT_MAX>
+template <typename T, int KG, int KW>
 __global__ __launch_bounds__(CNT, 1) void cfwd_kernel(CLoopArgs a) {
-  using S = CShape<T, KSW, NCT>;
-  constexpr int KPC = S::KPC, H = S::H, UX = S::UX, KC = S::KC, CW = S::CW, CT = S::CT;
-  constexpr int TPP = S::TPP, PW = S::PW, RB = S::RB, NPROD = S::NPROD, EPT = S::EPT;
-  constexpr int KG = 2, NG = 16, UN = 4 * NCT;
-  constexpr int KS = H / (4 * KPC);
-  constexpr int NPASS = (MRT_MAX + TPP - 1) / TPP;
-  static_assert(NPASS * KG <= 64, "one lane per partial flag");
-  constexpr long G4 = 4L * H, H5 = 5L * H;
-  __shared__ float4 red[2 * RB / 4];
-  __shared__ int win[2 * (CWIN + 1)];
-  __shared__ int sperm[MRT_MAX * 16];
+  using S = CShape<T, KG, KW>;
+  constexpr int KPC = S::KPC, NGX = S::NGX, CW = S::CW, RW = S::RW, RPK = S::RPK, RPL = S::RPL, NP = S::NP;
+  extern __shared__ uint4 lds[];
   __shared__ int s_info[2];
-
   join_group(a.rank_ctr, s_info);
   const int x = uni(s_info[0]), rank = uni(s_info[1]);
-  if (x >= 8 || rank >= 32 || a.H != H || a.MRT > MRT_MAX) {
+  const int H = a.H, B = a.B, RGN = a.RGN;
+  if (x >= 8 || rank >= 32 || RGN > RW || H > 8 * 16 * NGX) {
     c_fail(a);
     return;
   }
-  const int kq = rank / NG, nq = rank % NG;
+  const int gpx = (H / 16 + 7) / 8;              // column groups per XCD
+  const int kq = rank / NGX, nq = rank % NGX, grp = x * gpx + nq;
+  if (nq >= gpx || grp * 16 >= H) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
-  const int q = lane >> 4, l16 = lane & 15;
-  const int B = a.B, MRT = a.MRT;
-  const T* WT = reinterpret_cast<const T*>(a.W);
-  T* HH = reinterpret_cast<T*>(a.X);
-  const int kb0 = kq * (KC / (4 * KPC)) + wave * KSW;   // first k-step of this wave
-
-  // weight slice: lane column l16 of column tile ct is local column
-  // ct*16 + l16 = gate * UN + u
-  uint4 wr[NCT][KSW];
-#pragma unroll
-  for (int ct = 0; ct < NCT; ++ct) {
-    const int c = ct * 16 + l16;
-    const int g = c / UN, u = c - g * UN;
-    const T* wcol = WT + ((long)g * H + x * UX + nq * UN + u) * a.ldw + a.woff;
-#pragma unroll
-    for (int i = 0; i < KSW; ++i) wr[ct][i] = ld16(wcol + ((kb0 + i) * 4 + q) * KPC);
+  const int KS = H / 32, KSP = c_share<T>(KS, KW);   // k-steps of the slice; of a share, padded
+  const long G4 = 4L * H, H5 = 5L * H;
+  {
+    // weights: local column c = gate * 16 + u of unit grp * 16 + u
+    const T* WT = reinterpret_cast<const T*>(a.W) + a.woff + (long)kq * KS * 2 * KPC;
+    for (int i = tid; i < KW * KSP * 128; i += CNT) {
+      const int l = i & 63, c = ((i >> 6) & 1) * 32 + (l & 31), sh = (i >> 7) / KSP;
+      const int ks = sh * KS / KW + (i >> 7) - sh * KSP;
+      lds[i] = ks < (sh + 1) * KS / KW
+                   ? ld16(WT + (4L * (grp * 16 + (c & 15)) + (c >> 4)) * a.ldw + (2 * ks + (l >> 5)) * KPC)
+                   : zero4();
+    }
   }
-  for (int i = tid; i < MRT_MAX * 16; i += CNT) sperm[i] = i < B ? a.perm[i] : -1;
-
-  // cell thread: tile slot tp of a pass, row crow, unit jc
-  const int tp = uni(tid / CT), crow = (tid / CW) & 15, uu = tid % CW;
-  const int jc = x * UX + nq * UN + kq * CW + uu;
   __syncthreads();
-  float hs[NPASS], cs[NPASS];
+  const int rg = wave % RW, kw = wave / RW;
+  if (rg >= RGN) return;
+  float* sc = reinterpret_cast<float*>(lds + KW * KSP * 128) + wave * (kScratch / 4);
+  float* sc_h = sc;                    // [RPK][CW] h_t
+  float* sc_c = sc + RPK * CW;         // [RPK][CW] c_t
+
+  // cells of this wave: unit uu of the work-group's CW, rows lr .. lr + RPL - 1
+  const int uu = lane % CW, lr = kw * RPK + (lane / CW) * RPL;
+  const bool cellt = lane / CW < RPK / RPL;
+  const int jb = grp * 16 + kq * CW, j = jb + uu;
+  // row-wise stores: 16 bytes of the units of one row (h), four floats (y, c)
+  const int hr = kw * RPK + lane;                          // lanes < RPK
+  const int yr = kw * RPK + lane / (CW / 4), yc = (lane % (CW / 4)) * 4;
+  const bool hst = lane < RPK, yst = lane < RPK * (CW / 4);
+  const int yb = yst && rg * 32 + yr < B ? a.perm[rg * 32 + yr] : -1;
+  int b[RPL];
+  float hs[RPL], cs[RPL];
 #pragma unroll
-  for (int p = 0; p < NPASS; ++p) {
-    const int m = p * TPP + tp;
-    const int b = m < MRT ? sperm[m * 16 + crow] : -1;
-    hs[p] = (b >= 0 && a.h0) ? a.h0[(long)b * H + jc] : 0.f;
-    cs[p] = (b >= 0 && a.c0) ? a.c0[(long)b * H + jc] : 0.f;
+  for (int e = 0; e < RPL; ++e) {
+    const int r = rg * 32 + lr + e;
+    b[e] = cellt && r < B ? a.perm[r] : -1;
+    hs[e] = b[e] >= 0 && a.h0 ? a.h0[(long)b[e] * H + j] : 0.f;
+    cs[e] = b[e] >= 0 && a.c0 ? a.c0[(long)b[e] * H + j] : 0.f;
   }
 
   const int T_eff = uni(a.meta[0]);
-  const int t1 = min(a.T_max, T_eff);
-  int wlo = 0;
-  c_window(a, win, 0);
-  const __amdgpu_buffer_rsrc_t rring = make_rsrc(a.ring, (unsigned)(2 * MRT * KS) << 10);
-  const __amdgpu_buffer_rsrc_t rpart = make_rsrc(a.part, (unsigned)(2L * 8 * MRT * 32 * PW * 4));
+  const int len = group_len(a, rg, T_eff);
+  // this wave's k-steps of the slice and their producers' flags
+  const int ks0 = kw * KS / KW, nks = (kw + 1) * KS / KW - ks0;
+  const int ksg = kq * KS + ks0;                           // first k-step of the row group's H / (2 KPC)
+  const int KSR = KG * KS;
+  const unsigned* in_flags = a.xflags + ((long)rg * 256 + 2 * ksg) * KW;
+  const unsigned* grp_flags = a.xflags + ((long)rg * 256 + grp * KG) * KW;
+  unsigned* my_xflag = a.xflags + ((long)rg * 256 + grp * KG + kq) * KW + kw;
+  const long pbase = (((long)x * RGN + rg) * NGX + nq) * NP;
+  unsigned* my_pflag = a.pflags + pbase + kq * KW + kw;
+  float* my_part = a.part + (pbase + kq * KW + kw) * kPartFloats;
+  const __amdgpu_buffer_rsrc_t rpart = make_rsrc(a.part + pbase * kPartFloats, NP * kPartFloats * 4);
+  const __amdgpu_buffer_rsrc_t rring = make_rsrc(a.ring, (unsigned)(2 * RGN * KSR) << 10);
+  const uint4* w = lds + kw * KSP * 128;
+  // ring chunk of (row, the work-group's CW = KPC units)
+  const unsigned hoff = (unsigned)(((jb / (2 * KPC)) << 10) + (((jb / KPC) & 1) * 32 + hr) * 16);
 
-  // input projections of the cell thread's rows at step t
-  float zx[NPASS][4];
-  auto load_zx = [&](int t) {
-    const int A = uni(win[t - wlo]), off = uni(win[CWIN + 1 + t - wlo]);
-    const __amdgpu_buffer_rsrc_t rz = make_rsrc(a.Zx + (long)off * G4, (unsigned)(A * G4 * 4));
+  float4 zx[RPL];
+  auto load_zx = [&](int A, long off) {
+    const int nr = max(0, min(32, A - rg * 32));
+    const __amdgpu_buffer_rsrc_t rz = make_rsrc(a.Zx + (off + rg * 32) * G4, (unsigned)(nr * G4 * 4));
 #pragma unroll
-    for (int p = 0; p < NPASS; ++p) {
-      const int r = (p * TPP + tp) * 16 + crow;
-      const unsigned zo = r < A ? (unsigned)((r * G4 + jc) * 4) : kOOB;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) zx[p][g] = ld_f32(rz, zo + g * H * 4);
-    }
+    for (int e = 0; e < RPL; ++e)
+      zx[e] = ld_f32x4(rz, cellt ? (unsigned)(((lr + e) * G4 + 4 * j) * 4) : kOOB);
   };
-  // h history, stack row and y of step tt (A rows running from compact
-  // offset off), from the cell registers, after h_tt is published
-  float gv[NPASS][5];
-  auto flush = [&](int tt, int A, int off) {
-#pragma unroll
-    for (int p = 0; p < NPASS; ++p) {
-      const int m = p * TPP + tp, r = m * 16 + crow;
-      const bool act = r < A;
-      if (act) {
-        const long cr = off + r;
-        HH[cr * H + jc] = Op<T>::from_f32(hs[p]);
-        if (a.stack) {
-          float* st = a.stack + cr * H5 + jc;
-#pragma unroll
-          for (int c = 0; c < 5; ++c) st[(long)c * H] = gv[p][c];
-        }
-      }
-      if (a.y && m < MRT) {
-        const int b = sperm[r];
-        if (b >= 0) a.y[((long)tt * B + b) * H + jc] = act ? hs[p] : 0.f;
-      }
-    }
-  };
+  int A_t = len > 0 ? uni(a.active[0]) : 0;
+  long off_t = 0;
+  if (len > 0) load_zx(A_t, 0);
 
-  for (int t = 0; t < t1; ++t) {
-    if (t + 1 > wlo + CWIN) {
-      wlo = t;
-      c_window(a, win, wlo);
-    }
-    const int A_t = uni(win[t - wlo]), off_t = uni(win[CWIN + 1 + t - wlo]);
-    const int nt = (A_t + 15) >> 4;
-    const int sl = t & 1;
-
-    // ---- phase A: partial products of every running tile
-    // every producer of this wave's k-steps has published h_{t-1} of every
-    // running tile (one wait for all tiles: they are published together)
-    if (t > 0)
-      wait_tiles<NPROD, (MRT_MAX * NPROD + 63) / 64>(
-          a, a.xflags, nt, producer_of<UX, UN, CW, NG>(kb0 * 4 * KPC + (lane % NPROD) * CW), (unsigned)(t + 1));
-    auto load_a = [&](int m, uint4 (&v)[KSW]) {
-      const __amdgpu_buffer_rsrc_t rs =
-          make_rsrc(reinterpret_cast<char*>(a.ring) + ((long)((sl ^ 1) * MRT + m) * KS << 10), (unsigned)KS << 10);
+  for (int t = 0; t < len; ++t) {
+    const int A_n = uni(a.active[t + 1]);
+    const int nr = min(32, A_t - rg * 32);                 // rows of the group running at t
+    // ---- phase A
+    if (t > 0) wait_range(a, in_flags, 2 * nks * KW, (unsigned)(t + 1));
+    f32x16 acc[2] = {f32x16{}, f32x16{}};
+    float4 zc[RPL];
+    c_product<T>(make_rsrc(reinterpret_cast<char*>(a.ring) + (((long)((t + 1) & 1) * RGN + rg) * KSR + ksg) * 1024,
+                           (unsigned)nks << 10),
+                 w, KSP / c_unroll<T>(), nq, acc, [&]() {
 #pragma unroll
-      for (int i = 0; i < KSW; ++i) v[i] = ld_chunk_l2(rs, (unsigned)(((kb0 + i) << 10) + lane * 16));
-    };
-    // tile m: operands in cur; the operands of tile m+2 go to nxt2
-    auto tile = [&](int m, uint4 (&cur)[KSW], uint4 (&nxt2)[KSW]) {
-      if (m + 2 < nt) load_a(m + 2, nxt2);
-      // the input projections of this step, issued after the next tiles'
-      // operands so that the first products do not wait for them
-      if (m == 0) load_zx(t);
-      f32x4 acc[NCT];
-#pragma unroll
-      for (int ct = 0; ct < NCT; ++ct) acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int i = 0; i < KSW; ++i)
-#pragma unroll
-        for (int ct = 0; ct < NCT; ++ct) acc[ct] = Mfma<T>::step(cur[i], wr[ct][i], acc[ct]);
-      // LDS buffer m % 2: [wave][ct][lane] float4 (the lane's 4 result rows)
-      float4* rb = red + (m & 1) * (RB / 4);
-#pragma unroll
-      for (int ct = 0; ct < NCT; ++ct)
-        rb[(wave * NCT + ct) * 64 + lane] = make_float4(acc[ct][0], acc[ct][1], acc[ct][2], acc[ct][3]);
-      __syncthreads();
-      // column c = gate * UN + kc * CW + uu; partial layout
-      // [kc][row / 4][uu][row % 4][gate], so that a cell reads its 4 gates
-      // as one 16-byte load
-      float* pd = a.part + ((long)((sl * 8 + x) * MRT + m) * 32 + rank) * PW;
-      reduce_waves<NCT, EPT>(rb, [&](int c, int rq, int e, float v) {
-        const int g = c / UN, u = c - g * UN, kc = u / CW, ou = u - kc * CW;
-        pd[(((kc * 4 + rq) * CW + ou) * 4 + e) * 4 + g] = v;
-      });
-    };
-    // three operand buffers with fixed roles per unrolled tile, so that no
-    // register copy waits for a load in flight
-    uint4 a0[KSW], a1[KSW], a2[KSW];
-    load_a(0, a0);
-    if (nt > 1) load_a(1, a1);
-    for (int m = 0; m < nt; m += 3) {
-      tile(m, a0, a2);
-      if (m + 1 < nt) tile(m + 1, a1, a0);
-      if (m + 2 < nt) tile(m + 2, a2, a1);
-    }
+                   for (int e = 0; e < RPL; ++e) zc[e] = zx[e];
+                   load_zx(A_n, off_t + A_t);
+                 });
+    if (t > 0) wait_range(a, grp_flags, NP, (unsigned)(t + 1));
+    store_partial(my_part, acc);
     wait_all_vm();
-    __syncthreads();
-    if (tid < nt)
-      __hip_atomic_store(a.pflags + (x * MRT + tid) * 32 + rank, (unsigned)(t + 2), __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
-
-    // ---- phase B: the KG partial products of this N-group, cells
+    if (lane == 0) __hip_atomic_store(my_pflag, (unsigned)(t + 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    // ---- phase B
+    wait_range(a, a.pflags + pbase, NP, (unsigned)(t + 2));
+    float z[RPL][4];
     {
-      const int p = lane / KG, k = lane % KG;
-      const int m = p * TPP + tp;
-      wait_each(a, a.pflags, (x * MRT + m) * 32 + k * NG + nq, lane < NPASS * KG && m < nt, (unsigned)(t + 2));
-    }
-    float zs[NPASS][4];
+      float pv[NP][4][RPL];
 #pragma unroll
-    for (int p = 0; p < NPASS; ++p) {
-      const int m = p * TPP + tp;
+      for (int p = 0; p < NP; ++p)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) zs[p][g] = zx[p][g];
-      if (m < nt) {
-        const long base = (long)((sl * 8 + x) * MRT + m) * 32 * PW;
+        for (int g = 0; g < 4; ++g)
+          load_partial<RPL>(rpart, p * kPartFloats * 4 + part_off(g * 16 + kq * CW + uu, lr & 31), pv[p][g]);
 #pragma unroll
-        for (int k = 0; k < KG; ++k) {
-          const uint4 v = ld_chunk_l2(rpart, (unsigned)((base + (long)(k * NG + nq) * PW +
-                                                         (((kq * 4 + (crow >> 2)) * CW + uu) * 4 + (crow & 3)) * 4) *
-                                                        4));
-          zs[p][0] += __uint_as_float(v.x);
-          zs[p][1] += __uint_as_float(v.y);
-          zs[p][2] += __uint_as_float(v.z);
-          zs[p][3] += __uint_as_float(v.w);
-        }
+      for (int e = 0; e < RPL; ++e) {
+        z[e][0] = zc[e].x;
+        z[e][1] = zc[e].y;
+        z[e][2] = zc[e].z;
+        z[e][3] = zc[e].w;
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) z[e][g] += pv[p][g][e];
       }
     }
 #pragma unroll
-    for (int p = 0; p < NPASS; ++p) {
-      const int m = p * TPP + tp, r = m * 16 + crow;
-      gv[p][0] = sigmoidf_(zs[p][0]);
-      gv[p][1] = sigmoidf_(zs[p][1]);
-      gv[p][2] = tanhf_(zs[p][2]);
-      gv[p][3] = sigmoidf_(zs[p][3]);
-      gv[p][4] = gv[p][1] * cs[p] + gv[p][0] * gv[p][2];
-      if (m < nt && r < A_t) {
-        cs[p] = gv[p][4];
-        hs[p] = gv[p][3] * tanhf_(gv[p][4]);
-        st_dev(rring, ring_off<T>(sl, MRT, KS, m, crow, jc), Op<T>::from_f32(hs[p]));
+    for (int e = 0; e < RPL; ++e) {
+      z[e][0] = sigmoidf_(z[e][0]);
+      z[e][1] = sigmoidf_(z[e][1]);
+      z[e][2] = tanhf_(z[e][2]);
+      z[e][3] = sigmoidf_(z[e][3]);
+      const float cn = z[e][1] * cs[e] + z[e][0] * z[e][2];
+      const float hn = z[e][3] * tanhf_(cn);
+      if (lr + e < nr) {
+        cs[e] = cn;
+        hs[e] = hn;
       }
+      if (cellt) {
+        sc_h[(lr - kw * RPK + e) * CW + uu] = hs[e];
+        sc_c[(lr - kw * RPK + e) * CW + uu] = cs[e];
+      }
+    }
+    wave_lds_fence();
+    uint4 hv = zero4();
+    if (hst) {
+      const float4* s4 = reinterpret_cast<const float4*>(sc_h + lane * CW);
+      if constexpr (sizeof(T) == 4) {
+        hv = __builtin_bit_cast(uint4, s4[0]);
+      } else {
+        const float4 u = s4[0], v = s4[1];
+        hv.x = (unsigned)f32_to_bf16(u.x) | ((unsigned)f32_to_bf16(u.y) << 16);
+        hv.y = (unsigned)f32_to_bf16(u.z) | ((unsigned)f32_to_bf16(u.w) << 16);
+        hv.z = (unsigned)f32_to_bf16(v.x) | ((unsigned)f32_to_bf16(v.y) << 16);
+        hv.w = (unsigned)f32_to_bf16(v.z) | ((unsigned)f32_to_bf16(v.w) << 16);
+      }
+      if (hr < nr) st16_dev(rring, (unsigned)(((t & 1) * RGN + rg) * KSR) * 1024u + hoff, hv);
     }
     wait_all_vm();
-    __syncthreads();
-    if (tid < nt)
-      __hip_atomic_store(a.xflags + tid * 256 + x * 32 + rank, (unsigned)(t + 2), __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
-    flush(t, A_t, off_t);
+    if (lane == 0) __hip_atomic_store(my_xflag, (unsigned)(t + 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // h history, stack row and y of step t
+    const long cr0 = off_t + rg * 32;
+    if (hst && hr < nr) *reinterpret_cast<uint4*>(reinterpret_cast<T*>(a.X) + (cr0 + hr) * H + jb) = hv;
+    if (a.stack) {
+#pragma unroll
+      for (int e = 0; e < RPL; ++e)
+        if (cellt && lr + e < nr)
+          *reinterpret_cast<float4*>(a.stack + (cr0 + lr + e) * H5 + 4 * j) =
+              make_float4(z[e][0], z[e][1], z[e][2], z[e][3]);
+      if (yst && yr < nr)
+        *reinterpret_cast<float4*>(a.stack + (cr0 + yr) * H5 + G4 + jb + yc) =
+            *reinterpret_cast<const float4*>(sc_c + (yr - kw * RPK) * CW + yc);
+    }
+    if (a.y && yb >= 0)
+      *reinterpret_cast<float4*>(a.y + ((long)t * B + yb) * H + jb + yc) =
+          yr < nr ? *reinterpret_cast<const float4*>(sc_h + (yr - kw * RPK) * CW + yc) : make_float4(0.f, 0.f, 0.f, 0.f);
+    wave_lds_fence();
+    off_t += A_t;
+    A_t = A_n;
   }
 
 #pragma unroll
-  for (int p = 0; p < NPASS; ++p) {
-    const int m = p * TPP + tp;
-    const int b = m < MRT ? sperm[m * 16 + crow] : -1;
-    if (b < 0) continue;
-    a.hT[(long)b * H + jc] = hs[p];
-    a.cT[(long)b * H + jc] = cs[p];
-    if (a.y)
-      for (int t = max(T_eff, 0); t < a.T_max; ++t) a.y[((long)t * B + b) * H + jc] = 0.f;
+  for (int e = 0; e < RPL; ++e) {
+    if (b[e] < 0) continue;
+    a.hT[(long)b[e] * H + j] = hs[e];
+    a.cT[(long)b[e] * H + j] = cs[e];
+  }
+  // y past the group's last step: whole rows, the steps dealt to the column
+  // groups' work-groups, the rows to the waves of the slice
+  if (a.y) {
+    const int nwg = (H / 16) * KG, wg = grp * KG + kq;
+    const int rows = min(32, B - rg * 32);
+    for (int t = len + wg; t < a.T_max; t += nwg)
+      for (int r = kw; r < rows; r += KW) {
+        float4* row = reinterpret_cast<float4*>(a.y + ((long)t * B + a.perm[rg * 32 + r]) * H);
+        for (int i = lane; i < H / 4; i += 64) row[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      }
   }
 }
 
 // ---------------------------------------------------------------------------
 // Gradient loop, chip-wide.  Step t (descending):
-//   phase B': dh_t of the rows that ran at step t+1 is the sum of the KG
+//   phase B': dh_t of the rows that ran at step t+1 is the sum of the KG KW
 //     partial products of step t+1 (other rows keep dhT); with the values
 //     popped for step t: dh_tot, dc, dz; dz into the ring, publish; then the
-//     dz rows for the dW and dx products and db; pops of step t-1 issued;
-//   phase A': partial products of dh_{t-1} = dz_t W_h^T for every running
-//     tile, published at once.
+//     dz rows for the dW and dx products and db;
+//   phase A': partial products of dh_{t-1} = dz_t W_h^T, published; the pops
+//     of step t-1 behind its last ring loads.
 // After the last step, dh0 of the rows that ran at step 0 is the sum of the
 // partial products of step 0.
 // ---------------------------------------------------------------------------
-template <typename T, int KSW, int NCT, int MRT_MAX>
+template <typename T, int KG, int KW>
 __global__ __launch_bounds__(CNT, 1) void cbwd_kernel(CLoopArgs a) {
-  using S = CShape<T, KSW, NCT>;
-  constexpr int KPC = S::KPC, H = S::H, UX = S::UX, KC = S::KC, CW = S::CW, CT = S::CT;
-  constexpr int TPP = S::TPP, PW = S::PW, RB = S::RB, NPROD = S::NPROD, EPT = S::EPT;
-  constexpr int KG = 8, NG = 4, UN = 16 * NCT;
-  constexpr int KS = 4 * H / (4 * KPC);
-  constexpr int NPASS = (MRT_MAX + TPP - 1) / TPP;
-  static_assert(NPASS * KG <= 64, "one lane per partial flag");
-  constexpr long G4 = 4L * H, H5 = 5L * H;
-  __shared__ float4 red[2 * RB / 4];
-  __shared__ int win[2 * (CWIN + 1)];
-  __shared__ int sperm[MRT_MAX * 16];
+  using S = CShape<T, KG, KW>;
+  constexpr int KPC = S::KPC, NGX = S::NGX, CW = S::CW, RW = S::RW, RPK = S::RPK, RPL = S::RPL, NP = S::NP;
+  extern __shared__ uint4 lds[];
   __shared__ int s_info[2];
-
   join_group(a.rank_ctr, s_info);
   const int x = uni(s_info[0]), rank = uni(s_info[1]);
-  if (x >= 8 || rank >= 32 || a.H != H || a.MRT > MRT_MAX) {
+  const int H = a.H, B = a.B, RGN = a.RGN;
+  if (x >= 8 || rank >= 32 || RGN > RW || H > 8 * 64 * NGX) {
     c_fail(a);
     return;
   }
-  const int kq = rank / NG, nq = rank % NG;
+  const int ngr = (H + 63) / 64;
+  const int gpx = (ngr + 7) / 8;
+  const int kq = rank / NGX, nq = rank % NGX, grp = x * gpx + nq;
+  if (nq >= gpx || grp >= ngr) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
-  const int q = lane >> 4, l16 = lane & 15;
-  const int B = a.B, MRT = a.MRT;
+  const int KS = H / 32, KSP = c_share<T>(KS, KW);   // k-steps of the slice (of 4H columns); of a share, padded
+  const long G4 = 4L * H, H5 = 5L * H;
   const T* W = reinterpret_cast<const T*>(a.W);
-  T* DZ = reinterpret_cast<T*>(a.X);
-  const int kb0 = kq * (KC / (4 * KPC)) + wave * KSW;   // first dz k-step of this wave
-
-  // weight slice: output column ct*16 + l16 is unit x UX + nq UN + ct*16 + l16;
-  // the product's reduction runs over the 4H columns of W
-  uint4 wr[NCT][KSW];
+  {
+    // weights: output column c is unit grp * 64 + c; element k of a row is
+    // W[unit][gate k % 4][unit' k / 4].  Eight neighbouring threads take
+    // neighbouring chunks of one row (coalesced reads of each gate's run).
+    constexpr int UPC = KPC / 4;                 // units per chunk
+    typedef typename std::conditional<sizeof(T) == 2, unsigned, float>::type P4;   // a chunk's values of one gate
+    const int nch = KS * 2;                      // chunks per row of the slice
+    for (int i = tid; i < KW * KSP * 128; i += CNT) lds[i] = zero4();   // (the padding)
+    __syncthreads();
+    for (int i = tid; i < (nch + 7) / 8 * 512; i += CNT) {
+      const int c8 = i & 7, c = (i >> 3) & 63, ch = (i >> 9) * 8 + c8;
+      if (ch >= nch) continue;
+      const int unit = grp * 64 + c;
+      uint4 v = zero4();
+      if (unit < H) {
+        const T* src = W + (long)(a.woff + unit) * G4 + (long)(kq * nch + ch) * UPC;
+        alignas(16) T tmp[KPC];
 #pragma unroll
-  for (int ct = 0; ct < NCT; ++ct) {
-    const T* wrow = W + (long)(a.woff + x * UX + nq * UN + ct * 16 + l16) * G4;
+        for (int g = 0; g < 4; ++g) {
+          const P4 p = *reinterpret_cast<const P4*>(src + (long)g * H);
+          if constexpr (sizeof(T) == 2) {
+            tmp[g] = (T)(p & 0xffffu);
+            tmp[4 + g] = (T)(p >> 16);
+          } else {
+            tmp[g] = p;
+          }
+        }
+        v = *reinterpret_cast<const uint4*>(tmp);
+      }
+      const int ks = ch >> 1;
+        int sh = 0;   // the share of k-step ks
 #pragma unroll
-    for (int i = 0; i < KSW; ++i) wr[ct][i] = ld16(wrow + ((kb0 + i) * 4 + q) * KPC);
+        for (int k = 1; k < KW; ++k) sh += ks >= k * KS / KW;
+        lds[((sh * KSP + ks - sh * KS / KW) * 2 + (c >> 5)) * 64 + (ch & 1) * 32 + (c & 31)] = v;
+    }
   }
-  for (int i = tid; i < MRT_MAX * 16; i += CNT) sperm[i] = i < B ? a.perm[i] : -1;
-
-  const int tp = uni(tid / CT), crow = (tid / CW) & 15, uu = tid % CW;
-  const int jc = x * UX + nq * UN + kq * CW + uu;
   __syncthreads();
-  float dh[NPASS], dc[NPASS];
+  const int rg = wave % RW, kw = wave / RW;
+  float* sc = reinterpret_cast<float*>(lds + KW * KSP * 128) + wave * (kScratch / 4);
+  T* sc_dz = reinterpret_cast<T*>(sc);           // [RPK][4][CW] dz of the wave's cells
+
+  const int uu = lane % CW, lr = kw * RPK + (lane / CW) * RPL;
+  const int jb = grp * 64 + kq * CW, j = jb + uu;
+  const bool has = rg < RGN && jb < H;           // the wave has cells (H % CW == 0: all of its units)
+  const bool cellt = has && lane / CW < RPK / RPL;
+  int b[RPL];
+  float dh[RPL], dc[RPL];
 #pragma unroll
-  for (int p = 0; p < NPASS; ++p) {
-    const int m = p * TPP + tp;
-    const int b = m < MRT ? sperm[m * 16 + crow] : -1;
-    dh[p] = (b >= 0 && a.dhT) ? a.dhT[(long)b * H + jc] : 0.f;
-    dc[p] = (b >= 0 && a.dcT) ? a.dcT[(long)b * H + jc] : 0.f;
+  for (int e = 0; e < RPL; ++e) {
+    const int r = rg * 32 + lr + e;
+    b[e] = cellt && r < B ? a.perm[r] : -1;
+    dh[e] = b[e] >= 0 && a.dhT ? a.dhT[(long)b[e] * H + j] : 0.f;
+    dc[e] = b[e] >= 0 && a.dcT ? a.dcT[(long)b[e] * H + j] : 0.f;
   }
   float dbacc[4] = {0.f, 0.f, 0.f, 0.f};
 
   const int T_eff = uni(a.meta[0]);
-  const int t1 = min(a.T_max, T_eff);
-  // the window covers steps t-2 .. t+1 of every step t
-  int wlo = t1 + 1 - CWIN > 0 ? t1 + 1 - CWIN : 0;
-  c_window(a, win, wlo);
-  const __amdgpu_buffer_rsrc_t rring = make_rsrc(a.ring, (unsigned)(2 * MRT * KS) << 10);
-  const __amdgpu_buffer_rsrc_t rpart = make_rsrc(a.part, (unsigned)(2L * 8 * MRT * 32 * PW * 4));
+  const int len = rg < RGN ? group_len(a, rg, T_eff) : 0;
+  const int ks0 = kw * KS / KW, nks = (kw + 1) * KS / KW - ks0;
+  const int ksg = kq * KS + ks0;
+  const int KSR = KG * KS;
+  // producers of the wave's k-steps: a k-step is KPC / 2 units, half of a
+  // work-group's CW
+  const int cb0 = ksg >> 1, cbn = ((ksg + nks - 1) >> 1) - cb0 + 1;
+  const unsigned* in_flags = a.xflags + ((long)rg * 256 + cb0) * KW;
+  const unsigned* grp_flags = a.xflags + ((long)rg * 256 + grp * KG) * KW;
+  unsigned* my_xflag = a.xflags + ((long)rg * 256 + grp * KG + kq) * KW + kw;
+  const long pbase = (((long)x * RGN + rg) * NGX + nq) * NP;
+  unsigned* my_pflag = a.pflags + pbase + kq * KW + kw;
+  float* my_part = a.part + (pbase + kq * KW + kw) * kPartFloats;
+  const __amdgpu_buffer_rsrc_t rpart = make_rsrc(a.part + pbase * kPartFloats, NP * kPartFloats * 4);
+  const __amdgpu_buffer_rsrc_t rring = make_rsrc(a.ring, (unsigned)(2 * RGN * KSR) << 10);
+  const uint4* w = lds + kw * KSP * 128;
+  T* DZ = reinterpret_cast<T*>(a.X);
 
-  // pops of step tt for the cell thread's rows: i, f, g, o, c_t, c_{t-1}, dy
-  float pv[NPASS][7];
-  auto fetch = [&](int tt) {
-    const int A = uni(win[tt - wlo]), off = uni(win[CWIN + 1 + tt - wlo]);
-    const int offp = tt > 0 ? uni(win[CWIN + 1 + tt - 1 - wlo]) : 0;
-    const __amdgpu_buffer_rsrc_t rs = make_rsrc(a.stack + (long)off * H5, (unsigned)(A * H5 * 4));
-    const __amdgpu_buffer_rsrc_t rp2 =
-        make_rsrc(a.stack + (long)offp * H5 + 4L * H, tt > 0 ? (unsigned)(A * H5 * 4) : 0u);
-    const __amdgpu_buffer_rsrc_t rc = make_rsrc(a.c0, (tt == 0 && a.c0) ? (unsigned)(B * H * 4) : 0u);
+  // popped for the step at hand: i, f, g, o; c_{t-1}; dy.  c_t is the c_{t-1}
+  // of the step after it.
+  float4 gt[RPL];
+  float cc[RPL], cp[RPL], dyv[RPL];
+  auto load_c = [&](float (&v)[RPL], int t, int A, long off) {   // c_t of the rows running at t (t < 0: c0)
+    const int nr = max(0, min(32, A - rg * 32));
+    const __amdgpu_buffer_rsrc_t rc = t >= 0 ? make_rsrc(a.stack + (off + rg * 32) * H5 + G4, (unsigned)(nr * H5 * 4))
+                                             : make_rsrc(a.c0, a.c0 ? (unsigned)((long)B * H * 4) : 0u);
+#pragma unroll
+    for (int e = 0; e < RPL; ++e)
+      v[e] = ld_f32(rc, b[e] < 0 ? kOOB : (unsigned)(((t >= 0 ? (lr + e) * H5 : (long)b[e] * H) + j) * 4));
+  };
+  auto load_step = [&](int t, int A, long off) {
+    const int nr = max(0, min(32, A - rg * 32));
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(a.stack + (off + rg * 32) * H5, (unsigned)(nr * H5 * 4));
     const __amdgpu_buffer_rsrc_t rd =
-        a.dy_compact ? make_rsrc(a.dy + (long)off * H, (unsigned)(A * H * 4))
-                     : make_rsrc(a.dy ? a.dy + (long)tt * B * H : nullptr, a.dy ? (unsigned)(B * H * 4) : 0u);
+        a.dy_compact ? make_rsrc(a.dy + (off + rg * 32) * H, (unsigned)(nr * H * 4))
+                     : make_rsrc(a.dy ? a.dy + (long)t * B * H : nullptr, a.dy ? (unsigned)((long)B * H * 4) : 0u);
 #pragma unroll
-    for (int p = 0; p < NPASS; ++p) {
-      const int m = p * TPP + tp, r = m * 16 + crow;
-      const bool ok = r < A;
-      const int b = m < MRT ? sperm[r] : 0;
-      const unsigned so = ok ? (unsigned)((r * H5 + jc) * 4) : kOOB;
-#pragma unroll
-      for (int c = 0; c < 5; ++c) pv[p][c] = ld_f32(rs, so + c * H * 4);
-      pv[p][5] = tt > 0 ? ld_f32(rp2, so) : ld_f32(rc, ok ? (unsigned)((b * H + jc) * 4) : kOOB);
-      pv[p][6] = ld_f32(rd, ok ? (unsigned)((a.dy_compact ? r * H + jc : b * H + jc) * 4) : kOOB);
+    for (int e = 0; e < RPL; ++e) {
+      gt[e] = ld_f32x4(rs, b[e] < 0 ? kOOB : (unsigned)(((lr + e) * H5 + 4 * j) * 4));
+      dyv[e] = ld_f32(rd, b[e] < 0 ? kOOB : (unsigned)(((a.dy_compact ? (long)(lr + e) * H : (long)b[e] * H) + j) * 4));
     }
   };
-  // dh of the rows that ran at step tt from the partial products of that
-  // step (slot tt % 2); A_tt rows, value T_eff - tt
-  auto gather_dh = [&](int tt, int A_tt) {
-    const int ntt = (A_tt + 15) >> 4;
-    {
-      const int p = lane / KG, k = lane % KG;
-      const int m = p * TPP + tp;
-      wait_each(a, a.pflags, (x * MRT + m) * 32 + k * NG + nq, lane < NPASS * KG && m < ntt,
-                (unsigned)(T_eff - tt));
+  // dh of the rows that ran at step t from the partial products of that step
+  auto gather_dh = [&](int t, int nr) {
+    wait_range(a, a.pflags + pbase, NP, (unsigned)(T_eff - t));
+    constexpr int PB = NP * RPL > 32 ? 32 / RPL : NP;   // partials loaded at a time
+    float s[RPL];
+#pragma unroll
+    for (int p0 = 0; p0 < NP; p0 += PB) {
+      float pv[PB][RPL];
+#pragma unroll
+      for (int p = 0; p < PB; ++p)
+        load_partial<RPL>(rpart, (p0 + p) * kPartFloats * 4 + part_off(kq * CW + uu, lr & 31), pv[p]);
+#pragma unroll
+      for (int p = 0; p < PB; ++p)
+#pragma unroll
+        for (int e = 0; e < RPL; ++e) s[e] = p0 + p == 0 ? pv[p][e] : s[e] + pv[p][e];
+      __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int p = 0; p < NPASS; ++p) {
-      const int m = p * TPP + tp, r = m * 16 + crow;
-      if (m < ntt) {
-        const long base = (long)(((tt & 1) * 8 + x) * MRT + m) * 32 * PW;
-        float s = 0.f;
-#pragma unroll
-        for (int k = 0; k < KG; ++k)
-          s += ld_f32_l2(rpart, (unsigned)((base + (long)(k * NG + nq) * PW +
-                                            ((kq * 4 + (crow >> 2)) * CW + uu) * 4 + (crow & 3)) * 4));
-        if (r < A_tt) dh[p] = s;
-      }
-    }
+    for (int e = 0; e < RPL; ++e)
+      if (lr + e < nr) dh[e] = s[e];
   };
 
-  if (t1 > 0) fetch(t1 - 1);
-  for (int t = t1 - 1; t >= 0; --t) {
-    if (t - 2 < wlo && wlo > 0) {
-      wlo = t + 1 - CWIN > 0 ? t + 1 - CWIN : 0;
-      c_window(a, win, wlo);
+  if (len > 0) {
+    int A_t = uni(a.active[len - 1]), A_p = len > 1 ? uni(a.active[len - 2]) : 0, nr_next = 0;
+    long off_t = uni(a.off[len - 1]);
+    if (has) {
+      load_c(cc, len - 1, A_t, off_t);
+      load_step(len - 1, A_t, off_t);
+      load_c(cp, len - 2, A_p, off_t - A_p);
     }
-    const int A_t = uni(win[t - wlo]), off_t = uni(win[CWIN + 1 + t - wlo]);
-    const int nt = (A_t + 15) >> 4;
-    const int sl = t & 1;
-
-    // ---- phase B'
-    if (t + 1 < t1) gather_dh(t + 1, uni(win[t + 1 - wlo]));
-    float dz[NPASS][4];
+    for (int t = len - 1; t >= 0; --t) {
+      const int nr = min(32, A_t - rg * 32);
+      const int sl = t & 1;
+      const int A_pp = t >= 2 ? uni(a.active[t - 2]) : 0;
+      // ---- phase B'
+      if (has) {
+        if (t < len - 1) gather_dh(t + 1, nr_next);
+        float dz[RPL][4];
 #pragma unroll
-    for (int p = 0; p < NPASS; ++p) {
-      const int m = p * TPP + tp, r = m * 16 + crow;
+        for (int e = 0; e < RPL; ++e) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) dz[p][g] = 0.f;
-      if (m < nt && r < A_t) {
-        const float dht = dh[p] + pv[p][6];
-        const float ig = pv[p][0], fg = pv[p][1], gg = pv[p][2], og = pv[p][3];
-        const float c = pv[p][4], cp = pv[p][5];
-        const float tc = tanhf_(c);
-        const float d_o = dht * tc;
-        const float dct = dc[p] + dht * og * (1.f - tc * tc);
-        dz[p][0] = dct * gg * (ig * (1.f - ig));
-        dz[p][1] = dct * cp * (fg * (1.f - fg));
-        dz[p][2] = dct * ig * (1.f - gg * gg);
-        dz[p][3] = d_o * (og * (1.f - og));
-        dc[p] = dct * fg;
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-          st_dev(rring, ring_off<T>(sl, MRT, KS, m, crow, g * H + jc), Op<T>::from_f32(dz[p][g]));
-      }
-    }
-    wait_all_vm();
-    __syncthreads();
-    if (tid < nt)
-      __hip_atomic_store(a.xflags + tid * 256 + x * 32 + rank, (unsigned)(T_eff - t), __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-    for (int p = 0; p < NPASS; ++p) {
-      const int m = p * TPP + tp, r = m * 16 + crow;
-      if (m < nt && r < A_t) {
-        T* dzr = DZ + (long)(off_t + r) * G4 + jc;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          dzr[(long)g * H] = Op<T>::from_f32(dz[p][g]);
-          dbacc[g] += dz[p][g];
+          for (int g = 0; g < 4; ++g) dz[e][g] = 0.f;
+          if (lr + e < nr && cellt) {
+            const float dht = dh[e] + dyv[e];
+            const float ig = gt[e].x, fg = gt[e].y, gg = gt[e].z, og = gt[e].w;
+            const float tc = tanhf_(cc[e]);
+            const float d_o = dht * tc;
+            const float dct = dc[e] + dht * og * (1.f - tc * tc);
+            dz[e][0] = dct * gg * (ig * (1.f - ig));
+            dz[e][1] = dct * cp[e] * (fg * (1.f - fg));
+            dz[e][2] = dct * ig * (1.f - gg * gg);
+            dz[e][3] = d_o * (og * (1.f - og));
+            dc[e] = dct * fg;
+          }
         }
+        // ring: the four values of a unit side by side (bf16: two units per
+        // 16-byte chunk, put together by the lanes of a pair, which swap
+        // half of their rows)
+        const unsigned rbase = (unsigned)((sl * RGN + rg) * KSR) * 1024u;
+        if constexpr (sizeof(T) == 4) {
+#pragma unroll
+          for (int e = 0; e < RPL; ++e)
+            if (cellt && lr + e < nr)
+              st16_dev(rring, rbase + (unsigned)(((j >> 1) << 10) + ((j & 1) * 32 + lr + e) * 16),
+                       make_uint4(__float_as_uint(dz[e][0]), __float_as_uint(dz[e][1]), __float_as_uint(dz[e][2]),
+                                  __float_as_uint(dz[e][3])));
+        } else {
+          unsigned lo[RPL], hi[RPL];
+#pragma unroll
+          for (int e = 0; e < RPL; ++e) {
+            lo[e] = (unsigned)Op<T>::from_f32(dz[e][0]) | ((unsigned)Op<T>::from_f32(dz[e][1]) << 16);
+            hi[e] = (unsigned)Op<T>::from_f32(dz[e][2]) | ((unsigned)Op<T>::from_f32(dz[e][3]) << 16);
+          }
+          const unsigned ub = rbase + (unsigned)(((j >> 2) << 10) + (((j >> 1) & 1) * 32) * 16);
+          const bool odd = (uu & 1) != 0;
+          if constexpr (RPL == 1) {
+            typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+            if (cellt && lr < nr)
+              __builtin_amdgcn_raw_buffer_store_b64(u32x2{lo[0], hi[0]}, rring, ub + lr * 16 + (odd ? 8 : 0), 0,
+                                                    kCpolStoreDev);
+          } else {
+#pragma unroll
+            for (int e = 0; e < RPL / 2; ++e) {
+              // even lane: rows 0 .. RPL/2 - 1 of both units; odd lane: the rest
+              const int mine = odd ? RPL / 2 + e : e;
+              const unsigned ml = odd ? lo[RPL / 2 + e] : lo[e], mh = odd ? hi[RPL / 2 + e] : hi[e];
+              const unsigned gl = odd ? lo[e] : lo[RPL / 2 + e], gh = odd ? hi[e] : hi[RPL / 2 + e];
+              const unsigned ol = __shfl_xor(gl, 1, 64), oh = __shfl_xor(gh, 1, 64);
+              if (cellt && lr + mine < nr)
+                st16_dev(rring, ub + (lr + mine) * 16, odd ? make_uint4(ol, oh, ml, mh) : make_uint4(ml, mh, ol, oh));
+            }
+          }
+        }
+        wait_all_vm();
+        if (lane == 0) __hip_atomic_store(my_xflag, (unsigned)(T_eff - t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // dz rows (gate-major) through LDS: 16 bytes of one row and gate per lane
+#pragma unroll
+        for (int e = 0; e < RPL; ++e)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            dbacc[g] += dz[e][g];
+            if (cellt) sc_dz[((lr - kw * RPK + e) * 4 + g) * CW + uu] = Op<T>::from_f32(dz[e][g]);
+          }
+        wave_lds_fence();
+#pragma unroll
+        for (int i = 0; i < (RPK * 4 + 63) / 64; ++i) {
+          const int k = lane + 64 * i, row = kw * RPK + (k >> 2), g = k & 3;
+          if (k < RPK * 4 && row < nr)
+            *reinterpret_cast<uint4*>(DZ + (off_t + rg * 32 + row) * G4 + (long)g * H + jb) =
+                *reinterpret_cast<const uint4*>(sc_dz + k * CW);
+        }
+        wave_lds_fence();
+      } else {
+        // a work-group of the last, half-filled group without units of its
+        // own: nothing to publish, its flag only says how far it is
+        if (lane == 0) __hip_atomic_store(my_xflag, (unsigned)(T_eff - t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
+      // ---- phase A'
+      wait_range(a, in_flags, cbn * KW, (unsigned)(T_eff - t));
+      f32x16 acc[2] = {f32x16{}, f32x16{}};
+      c_product<T>(make_rsrc(reinterpret_cast<char*>(a.ring) + (((long)sl * RGN + rg) * KSR + ksg) * 1024,
+                             (unsigned)nks << 10),
+                   w, KSP / c_unroll<T>(), nq * 2, acc, [&]() {
+                     if (has && t >= 1) {   // pops of step t-1
+#pragma unroll
+                       for (int e = 0; e < RPL; ++e) cc[e] = cp[e];
+                       load_step(t - 1, A_p, off_t - A_p);
+                       load_c(cp, t - 2, A_pp, off_t - A_p - A_pp);
+                     }
+                   });
+      wait_range(a, grp_flags, NP, (unsigned)(T_eff - t));
+      store_partial(my_part, acc);
+      wait_all_vm();
+      if (lane == 0)
+        __hip_atomic_store(my_pflag, (unsigned)(T_eff - t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      nr_next = nr;
+      off_t -= A_p;
+      A_t = A_p;
+      A_p = A_pp;
     }
-
-    // ---- phase A': partial products of dh_{t-1}
-    // every producer of this wave's dz columns has published dz_t of every
-    // running tile (the wave's columns lie in one gate block)
-    wait_tiles<NPROD, (MRT_MAX * NPROD + 63) / 64>(
-        a, a.xflags, nt, producer_of<UX, UN, CW, NG>((kb0 * 4 * KPC + (lane % NPROD) * CW) % H),
-        (unsigned)(T_eff - t));
-    auto load_a = [&](int m, uint4 (&v)[KSW]) {
-      const __amdgpu_buffer_rsrc_t rs =
-          make_rsrc(reinterpret_cast<char*>(a.ring) + ((long)(sl * MRT + m) * KS << 10), (unsigned)KS << 10);
-#pragma unroll
-      for (int i = 0; i < KSW; ++i) v[i] = ld_chunk_l2(rs, (unsigned)(((kb0 + i) << 10) + lane * 16));
-    };
-    auto tile = [&](int m, uint4 (&cur)[KSW], uint4 (&nxt2)[KSW]) {
-      if (m + 2 < nt) load_a(m + 2, nxt2);
-      // pops of step t-1, issued after the next tiles' operands
-      if (m == 0 && t >= 1) fetch(t - 1);
-      f32x4 acc[NCT];
-#pragma unroll
-      for (int ct = 0; ct < NCT; ++ct) acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int i = 0; i < KSW; ++i)
-#pragma unroll
-        for (int ct = 0; ct < NCT; ++ct) acc[ct] = Mfma<T>::step(cur[i], wr[ct][i], acc[ct]);
-      float4* rb = red + (m & 1) * (RB / 4);
-#pragma unroll
-      for (int ct = 0; ct < NCT; ++ct)
-        rb[(wave * NCT + ct) * 64 + lane] = make_float4(acc[ct][0], acc[ct][1], acc[ct][2], acc[ct][3]);
-      __syncthreads();
-      // local unit c = kc * CW + uu; partial layout [kc][row / 4][uu][row % 4]
-      float* pd = a.part + ((long)((sl * 8 + x) * MRT + m) * 32 + rank) * PW;
-      reduce_waves<NCT, EPT>(rb, [&](int c, int rq, int e, float v) {
-        const int kc = c / CW, ou = c - kc * CW;
-        pd[((kc * 4 + rq) * CW + ou) * 4 + e] = v;
-      });
-    };
-    uint4 a0[KSW], a1[KSW], a2[KSW];
-    load_a(0, a0);
-    if (nt > 1) load_a(1, a1);
-    for (int m = 0; m < nt; m += 3) {
-      tile(m, a0, a2);
-      if (m + 1 < nt) tile(m + 1, a1, a0);
-      if (m + 2 < nt) tile(m + 2, a2, a1);
-    }
-    wait_all_vm();
-    __syncthreads();
-    if (tid < nt)
-      __hip_atomic_store(a.pflags + (x * MRT + tid) * 32 + rank, (unsigned)(T_eff - t), __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
+    if (has) gather_dh(0, nr_next);
   }
-  if (t1 > 0) gather_dh(0, uni(win[0 - wlo]));
 
 #pragma unroll
-  for (int p = 0; p < NPASS; ++p) {
-    const int m = p * TPP + tp;
-    const int b = m < MRT ? sperm[m * 16 + crow] : -1;
-    if (b < 0) continue;
-    if (a.dh0) a.dh0[(long)b * H + jc] = dh[p];
-    if (a.dc0) a.dc0[(long)b * H + jc] = dc[p];
+  for (int e = 0; e < RPL; ++e) {
+    if (b[e] < 0) continue;
+    if (a.dh0) a.dh0[(long)b[e] * H + j] = dh[e];
+    if (a.dc0) a.dc0[(long)b[e] * H + j] = dc[e];
   }
-  // db of the work-group's CW units (each unit's cell runs on exactly one
-  // work-group): sum over the cell threads of the unit, fixed order
+  // db of the work-group's CW units (each unit's cells run on exactly one
+  // work-group): sum over the waves and their row lanes, fixed order
   __syncthreads();
-  float* rf = reinterpret_cast<float*>(red);
+  float* red = reinterpret_cast<float*>(lds);
 #pragma unroll
-  for (int g = 0; g < 4; ++g) rf[g * CNT + tid] = dbacc[g];
+  for (int g = 0; g < 4; ++g) red[g * CNT + tid] = cellt ? dbacc[g] : 0.f;
   __syncthreads();
-  if (tid < 4 * CW) {
+  if (tid < 4 * CW && jb + tid % CW < H) {
     const int g = tid / CW, u = tid % CW;
     float s = 0.f;
-    for (int i = u; i < CNT; i += CW) s += rf[g * CNT + i];
-    a.db[(long)g * H + x * UX + nq * UN + kq * CW + u] = s;
+    for (int i = u; i < CNT; i += CW) s += red[g * CNT + i];
+    a.db[(long)g * H + jb + u] = s;
   }
 }
 
 // Set-up: h0 rows into ring slot 1 in the consumers' order, flags to zero.
-//   f = ((m * KS + ks) * 64 + l) * KPC + e: row m*16 + l % 16,
-//   unit ks * 4 KPC + (l / 16) * KPC + e.
+//   f = ((m * KS + ks) * 64 + l) * KPC + e: row m*32 + l % 32,
+//   unit (2 ks + l / 32) * KPC + e.
 template <typename T>
 __global__ __launch_bounds__(256) void c_prepare_kernel(const float* __restrict__ h0,
-                                                        const int* __restrict__ perm, int B, int H, int MRT,
+                                                        const int* __restrict__ perm, int B, int H, int RGN,
                                                         void* ring, unsigned* flags, int nflags) {
   constexpr int KPC = Op<T>::kPerChunk;
-  const int KS = H / (4 * KPC);
-  const long n = (long)MRT * KS * 64 * KPC;
+  const int KS = H / (2 * KPC);
+  const long n = (long)RGN * KS * 64 * KPC;
   T* slot1 = reinterpret_cast<T*>(ring) + n;
   for (long f = blockIdx.x * 256L + threadIdx.x; f < n; f += gridDim.x * 256L) {
     const int e = (int)(f % KPC);
     const int l = (int)((f / KPC) % 64);
     const int ks = (int)((f / (64 * KPC)) % KS);
     const int m = (int)(f / (64L * KPC * KS));
-    const int r = m * 16 + (l & 15);
-    const int u = ks * 4 * KPC + (l >> 4) * KPC + e;
+    const int r = m * 32 + (l & 31);
+    const int u = (2 * ks + (l >> 5)) * KPC + e;
     slot1[f] = Op<T>::from_f32((h0 && r < B) ? h0[(long)perm[r] * H + u] : 0.f);
   }
   for (long i = blockIdx.x * 256L + threadIdx.x; i < nflags; i += gridDim.x * 256L) flags[i] = 0u;
 }
 
 template <typename T>
-hipError_t launch_c_prepare(const float* h0, const int* perm, int B, int H, int mrt, void* ring,
+hipError_t launch_c_prepare(const float* h0, const int* perm, int B, int H, int rgn, void* ring,
                             unsigned* flags, int nflags, hipStream_t s) {
-  constexpr int KPC = Op<T>::kPerChunk;
-  const long n = (long)mrt * (H / (4 * KPC)) * 64 * KPC;
+  const long n = (long)rgn * 32 * H;
   long blocks = (std::max(n, (long)nflags) + 255) / 256;
   if (blocks > 4096) blocks = 4096;
   if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(c_prepare_kernel<T>, dim3((unsigned)blocks), dim3(256), 0, s, h0, perm, B, H, mrt, ring,
+  hipLaunchKernelGGL(c_prepare_kernel<T>, dim3((unsigned)blocks), dim3(256), 0, s, h0, perm, B, H, rgn, ring,
                      flags, nflags);
   return hipGetLastError();
 }
@@ -673,21 +787,30 @@ template hipError_t launch_c_prepare<float>(const float*, const int*, int, int, 
 template hipError_t launch_c_prepare<bf16_t>(const float*, const int*, int, int, int, void*, unsigned*, int,
                                              hipStream_t);
 
-// Kernels for a (dtype, H): bf16 H = 2048 (KSW 4, NCT 4), f32 H = 1024 (KSW 4,
-// NCT 2); up to 16 row tiles (B <= 256).
-template <typename T>
-CKernels c_kernels(int H, int mrt) {
-  constexpr bool bf = sizeof(T) == 2;
-  constexpr int NCT = bf ? 4 : 2;
-  using S = CShape<T, 4, NCT>;
+namespace {
+template <typename T, int KW>
+CKernels c_make(int H, int rgn) {
+  constexpr int KGF = sizeof(T) == 2 ? 2 : 4, KGB = 4 * KGF;
   CKernels k{};
-  if (H != S::H || mrt < 1 || mrt > 16) return k;
-  k.fwd = reinterpret_cast<const void*>(&cfwd_kernel<T, 4, NCT, 16>);
-  k.bwd = reinterpret_cast<const void*>(&cbwd_kernel<T, 4, NCT, 16>);
-  k.lds_fwd = 0;
-  k.lds_bwd = 0;
-  k.pw = S::PW;
+  k.fwd = reinterpret_cast<const void*>(&cfwd_kernel<T, KGF, KW>);
+  k.bwd = reinterpret_cast<const void*>(&cbwd_kernel<T, KGB, KW>);
+  k.lds = (size_t)KW * c_share<T>(H / 32, KW) * 2048 + CNW * kScratch;
+  k.rgn = rgn;
+  k.kw = KW;
+  k.cw = 16 / KGF;
+  k.part_floats = 8L * rgn * 32 * KW * kPartFloats;
+  k.flag_words = 8 + rgn * 256 * KW + 8 * rgn * 32 * KW;
   return k;
+}
+}  // namespace
+
+// Kernels for a (dtype, H, B): H % 32 == 0, one work-group per compute unit
+// for H = 2048 (bf16) / 1024 (f32), fewer below; at most 256 rows.
+template <typename T>
+CKernels c_kernels(int H, int B) {
+  const int rgn = (B + 31) / 32;
+  if (H % 32 || H < 64 || H > (sizeof(T) == 2 ? 2048 : 1024) || rgn < 1 || rgn > 8) return CKernels{};
+  return rgn <= 2 ? c_make<T, 4>(H, rgn) : rgn <= 4 ? c_make<T, 2>(H, rgn) : c_make<T, 1>(H, rgn);
 }
 template CKernels c_kernels<float>(int, int);
 template CKernels c_kernels<bf16_t>(int, int);
@@ -703,9 +826,13 @@ hipError_t c_setup(const CKernels& k, int* occ_fwd, int* occ_bwd) {
     *occ_bwd = 0;
     return hipSuccess;
   }
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(occ_fwd, k.fwd, CNT, 0);
+  e = hipFuncSetAttribute(k.fwd, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.lds);
   if (e != hipSuccess) return e;
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(occ_bwd, k.bwd, CNT, 0);
+  e = hipFuncSetAttribute(k.bwd, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.lds);
+  if (e != hipSuccess) return e;
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(occ_fwd, k.fwd, CNT, k.lds);
+  if (e != hipSuccess) return e;
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(occ_bwd, k.bwd, CNT, k.lds);
 }
 
 hipError_t c_launch(const void* fn, const CLoopArgs& a, size_t lds, hipStream_t s) {

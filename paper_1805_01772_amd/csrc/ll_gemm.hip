@@ -154,7 +154,7 @@ __global__ __launch_bounds__(256, 2) void gemm_nt_kernel(GemmArgs g) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int n = n0 + wn * 64 + j * 16 + l16;
-    bn[j] = bias && n < N ? bias[n] : 0.f;
+    bn[j] = bias && n < N ? bias[g.bias_um ? (n & 3) * g.bias_um + (n >> 2) : n] : 0.f;
   }
   int crows[4][4];
 #pragma unroll
@@ -369,7 +369,7 @@ __global__ __launch_bounds__(kBigThreads, 1) void gemm_nt_bf16_lds_kernel(GemmAr
 #pragma unroll
   for (int j = 0; j < NI; ++j) {
     const int n = n0 + wn * WN + j * 32 + l32;
-    bn[j] = bias && n < N ? bias[n] : 0.f;
+    bn[j] = bias && n < N ? bias[g.bias_um ? (n & 3) * g.bias_um + (n >> 2) : n] : 0.f;
   }
   int crows[MI][16];
 #pragma unroll

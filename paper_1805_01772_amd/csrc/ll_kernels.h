@@ -159,6 +159,7 @@ struct GemmArgs {
   long ldc;
   const int* c_rowmap;   // NULL: crow(m) = m
   const float* bias;     // NULL: none
+  int bias_um;           // > 0: columns in unit-major order, column n takes bias[(n % 4) * bias_um + n / 4]
   int M;                 // rows (capacity when M_dev is set)
   const int* M_dev;      // NULL or device scalar: rows actually present
   int N;
@@ -331,30 +332,32 @@ struct XLoopArgs {
 };
 
 // Chip-wide loops (ll_cloop.hip), for shapes whose recurrent weights need
-// more than one XCD: XCD x owns hidden units [x H/8, (x+1) H/8); its 32
-// work-groups split the reduction (K) and the units (N) of the recurrent
-// product.  Every row tile of the batch runs on every work-group.
+// more than one XCD: the work-groups of the chip split the columns and the
+// reduction of the recurrent product; every row of the batch runs on every
+// work-group, each wave taking rows of its own.
 struct CLoopArgs {
   int B, H, T_max;
-  int MRT;                // row tiles of the batch = ceil(B / 16)
+  int RGN;                // row groups of the batch = ceil(B / 32)
   const int* meta;
   const int* active;
   const int* off;
   const int* perm;
-  const void* W;          // forward: W^T [4H, ldw]; backward: W [rows, 4H]
+  const int* seq_len;
+  const void* W;          // forward: W^T [4H, ldw], row 4 u + g = gate g of unit u; backward: W [rows, 4H]
   int ldw;
   int woff;               // forward: column of the h part in W^T; backward: row of W_h
   void* X;                // forward: h history [cap, H]; backward: dz [cap, 4H] (operand type)
-  void* ring;             // exchange ring [2][MRT][ring_ks][1 KB] (forward: slot 1 holds h0)
-  int ring_ks;            // blocks per row tile: H / (4 KPC) forward, 4H / (4 KPC) backward
-  float* part;            // partial products [2][8][MRT][32][pw]
-  unsigned* xflags;       // exchange flags [MRT][256] (one per work-group and row tile)
-  unsigned* pflags;       // partial-product flags [8][MRT][32]
+  void* ring;             // exchange ring [2][RGN][H / (2 KPC) forward, 4H / (2 KPC) backward][1 KB]
+                          // (forward: slot 1 holds h0)
+  float* part;            // partial products [8][RGN][32][KW][32 x 64]
+  unsigned* xflags;       // exchange flags [RGN][256][KW] (one per cell block, row group and share)
+  unsigned* pflags;       // partial-product flags [8][RGN][32][KW]
   unsigned* rank_ctr;     // [8]
-  const float* Zx;        // forward: [cap, 4H]
+  const float* Zx;        // forward: [cap, 4H], column 4 u + g
   const float* h0;
   const float* c0;
-  float* stack;           // [cap, 5H] compact rows: forward push (NULL = inference), backward pop
+  float* stack;           // [cap, 5H] compact rows (gate g of unit u at 4 u + g, then c): forward push
+                          // (NULL = inference), backward pop
   float* y;
   float* hT;
   float* cT;
@@ -373,18 +376,21 @@ struct CLoopArgs {
 struct CKernels {
   const void* fwd;
   const void* bwd;
-  size_t lds_fwd;
-  size_t lds_bwd;
-  int pw;                 // partial floats per (work-group, row tile)
+  size_t lds;
+  int rgn;                // row groups of 32
+  int kw;                 // waves that share a reduction slice
+  int cw;                 // cell units per work-group
+  long part_floats;       // partial products
+  int flag_words;         // [8] rank counters, exchange flags [rgn][256][kw], partial flags [8][rgn][32][kw]
 };
 template <typename T>
-CKernels c_kernels(int H, int mrt);
+CKernels c_kernels(int H, int B);
 hipError_t c_setup(const CKernels& k, int* occ_fwd, int* occ_bwd);
 hipError_t c_launch(const void* fn, const CLoopArgs& a, size_t lds, hipStream_t s);
 // h0 rows (length order, operand type) into ring slot 1 and every flag and
 // rank counter of the launch to zero.
 template <typename T>
-hipError_t launch_c_prepare(const float* h0, const int* perm, int B, int H, int mrt, void* ring,
+hipError_t launch_c_prepare(const float* h0, const int* perm, int B, int H, int rgn, void* ring,
                             unsigned* flags, int nflags, hipStream_t s);
 
 struct XKernels {
@@ -443,6 +449,7 @@ struct TransposeJob {
   const void* in;
   void* out;
   int R, C, ldi, ldo, tiles_c, tiles;
+  int um;       // > 0: output row of column g um + u is 4 u + g (gate blocks of um units, unit-major)
 };
 struct FwdSetupArgs {
   PrepArgs prep;
@@ -452,7 +459,7 @@ struct FwdSetupArgs {
 template <typename T>
 hipError_t launch_fwd_setup(const int* seq_len, int B, int T_max, int* perm, int* active, int* off,
                             int* rowmap, int* meta, int* trip_out, int nw, const T* const* W, const int* R,
-                            int C, T* const* WT, hipStream_t s);
+                            int C, int um, T* const* WT, hipStream_t s);
 
 // Several independent small kernels in one launch (kernel launches cost a few
 // microseconds each on this GPU, small ones mostly that): each task runs on

@@ -154,11 +154,9 @@ struct ll_plan {
   // chip-wide loops (ll_cloop.hip): weights split over all XCDs
   bool cmode = false;
   ll::CKernels ck{};
-  int cMRT = 0;
   void* cring = nullptr;
   float* cpart = nullptr;
-  unsigned* cflags = nullptr;  // [8] rank counters, exchange flags [MRT][256], partial flags [8][MRT][32]
-  int cflag_words = 0;
+  unsigned* cflags = nullptr;  // rank counters, exchange and partial flags (ck.flag_words)
   // two-layer wavefront: one launch per direction runs both layers
   bool wave = false;
   ll::XKernels xk2{};
@@ -564,16 +562,14 @@ ll_status plan_configure(ll_plan* p, const ll_desc* desc, int device, const hipD
   }
 
   // Chip-wide loops where one XCD cannot hold the recurrent weights (bf16
-  // H = 2048, f32 H = 1024, B <= 256).
+  // H <= 2048, f32 H <= 1024, B <= 256).
   if (!p->xmode && allow && p->n_cu == 256) {
-    const int mrt = (B + 15) / 16;
-    ll::CKernels ck = p->bf16 ? ll::c_kernels<bf16_t>(H, mrt) : ll::c_kernels<float>(H, mrt);
-    if (ck.fwd && ck.bwd) {
+    ll::CKernels ck = p->bf16 ? ll::c_kernels<bf16_t>(H, B) : ll::c_kernels<float>(H, B);
+    if (ck.fwd && ck.bwd && ck.lds + 64 <= lds_limit) {
       int of = 0, ob = 0;
       if (ll::c_setup(ck, &of, &ob) == hipSuccess && of >= 1 && ob >= 1) {
         p->cmode = true;
         p->ck = ck;
-        p->cMRT = mrt;
       } else {
         (void)hipGetLastError();
       }
@@ -767,11 +763,10 @@ ll_status plan_layout(ll_plan* p, bool fwd_only, Take&& take) {
     }
   }
   if (p->cmode) {
-    // two slots x row tiles x (4H / k-step) blocks of 1 KB; partial products
-    ALLOC(p->cring, 2L * p->cMRT * (4L * H * (long)es / 64) * 1024, "exchange ring");
-    ALLOC(p->cpart, sizeof(float) * 2L * 8 * p->cMRT * 32 * p->ck.pw, "partial products");
-    p->cflag_words = 8 + p->cMRT * 256 + 8 * p->cMRT * 32;
-    ALLOC(p->cflags, sizeof(unsigned) * p->cflag_words, "exchange flags");
+    // two slots x row groups x (H or 4H columns / k-step) blocks of 1 KB; partial products
+    ALLOC(p->cring, 2L * p->ck.rgn * ((fwd_only ? 1L : 4L) * H * (long)es / 32) * 1024, "exchange ring");
+    ALLOC(p->cpart, sizeof(float) * p->ck.part_floats, "partial products");
+    ALLOC(p->cflags, sizeof(unsigned) * p->ck.flag_words, "exchange flags");
   }
   if (p->skip) ALLOC(p->sx, sizeof(float) * cap, "predicate input part");
   if (fwd_only) return LL_OK;   // the rest serves the saved stack and the gradient pass
@@ -998,7 +993,7 @@ ll_status ll_plan_geometry(const ll_plan* p, int32_t* nwg, int32_t* hj, int32_t*
   if (!p) return fail(LL_EINVAL, "plan is NULL");
   if (dw_in_place) *dw_in_place = (p->dw_rows[0] ? 1 : 0) | (p->dw_rows[1] ? 2 : 0);
   if (nwg) *nwg = (p->xmode || p->cmode) ? 256 : p->geom.nwg;
-  if (hj) *hj = p->xmode ? (p->bf16 ? 32 : 16) : p->cmode ? p->d.H / 256 : p->geom.HJ;
+  if (hj) *hj = p->xmode ? (p->bf16 ? 32 : 16) : p->cmode ? p->ck.cw : p->geom.HJ;
   if (rg) *rg = p->xmode ? 8 : p->cmode ? 1 : p->geom.RG;
   if (loop_form) *loop_form = p->xmode ? LL_LOOPS_XCD : p->cmode ? LL_LOOPS_CHIP : LL_LOOPS_GRID;
   if (wavefront) *wavefront = p->wave ? 1 : 0;
@@ -1015,7 +1010,7 @@ ll::CLoopArgs c_common(const ll_plan* p) {
   a.B = p->d.B;
   a.H = p->d.H;
   a.T_max = p->d.T_max;
-  a.MRT = p->cMRT;
+  a.RGN = p->ck.rgn;
   a.meta = p->meta;
   a.active = p->active;
   a.off = p->off;
@@ -1024,7 +1019,7 @@ ll::CLoopArgs c_common(const ll_plan* p) {
   a.part = p->cpart;
   a.rank_ctr = p->cflags;
   a.xflags = p->cflags + 8;
-  a.pflags = p->cflags + 8 + p->cMRT * 256;
+  a.pflags = p->cflags + 8 + p->ck.rgn * 256 * p->ck.kw;
   a.abort_flag = p->meta + 3;
   a.err = p->meta + 2;
   a.limit = p->barrier_ticks;
@@ -1160,7 +1155,7 @@ ll_status enqueue_fwd(ll_plan* p, hipStream_t s, const void* x, const int32_t* s
       R[l] = in_width(p, l) + H;
     }
     LL_HIP(ll::launch_fwd_setup<T>(seq_len, B, d.T_max, p->perm, p->active, p->off, p->rowmap, p->meta,
-                                   trip, L, Wl, R, p->G * H, WTl, s));
+                                   trip, L, Wl, R, p->G * H, p->cmode ? H : 0, WTl, s));
   }
   tend(p, s, LL_STAGE_PREP, ev);
   p->rows_prepared = false;
@@ -1181,6 +1176,7 @@ ll_status enqueue_fwd(ll_plan* p, hipStream_t s, const void* x, const int32_t* s
     g.C = p->Zx;
     g.ldc = (long)p->G * H;
     g.bias = bias[l];
+    g.bias_um = p->cmode ? H : 0;   // (W^T's rows are unit-major for the chip-wide loop)
     g.M = (int)p->cap;
     g.M_dev = p->meta + 1;
     g.N = p->G * H;
@@ -1328,14 +1324,14 @@ ll_status enqueue_fwd(ll_plan* p, hipStream_t s, const void* x, const int32_t* s
     if (p->cmode) {
       const float* hin = h0 ? h0 + (long)l * B * H : nullptr;
       ev = tbeg(p, s, LL_STAGE_LOOP_SETUP);
-      LL_HIP(ll::launch_c_prepare<T>(hin, p->perm, B, H, p->cMRT, p->cring, p->cflags, p->cflag_words, s));
+      LL_HIP(ll::launch_c_prepare<T>(hin, p->perm, B, H, p->ck.rgn, p->cring, p->cflags, p->ck.flag_words, s));
       tend(p, s, LL_STAGE_LOOP_SETUP, ev);
       ll::CLoopArgs ca = c_common(p);
       ca.W = p->WT[l];
       ca.ldw = Il + H;
       ca.woff = Il;
       ca.X = p->HH[l];
-      ca.ring_ks = (int)((long)H * p->es / 64);
+      ca.seq_len = seq_len;
       ca.Zx = p->Zx;
       ca.h0 = hin;
       ca.c0 = c0 ? c0 + (long)l * B * H : nullptr;
@@ -1344,7 +1340,7 @@ ll_status enqueue_fwd(ll_plan* p, hipStream_t s, const void* x, const int32_t* s
       ca.hT = hT + (long)l * B * H;
       ca.cT = cT + (long)l * B * H;
       ev = tbeg(p, s, LL_STAGE_FWD_LOOP);
-      LL_HIP(chained_loop_launch(p->device, s, [&] { return ll::c_launch(p->ck.fwd, ca, p->ck.lds_fwd, s); }));
+      LL_HIP(chained_loop_launch(p->device, s, [&] { return ll::c_launch(p->ck.fwd, ca, p->ck.lds, s); }));
       tend(p, s, LL_STAGE_FWD_LOOP, ev);
       continue;
     }
@@ -2019,14 +2015,14 @@ ll_status enqueue_bwd(ll_plan* p, hipStream_t s, const float* dy, const float* d
     }
     if (p->cmode) {
       ev = tbeg(p, s, LL_STAGE_LOOP_SETUP);
-      LL_HIP(setup.zero_u32(p->cflags, p->cflag_words));
+      LL_HIP(setup.zero_u32(p->cflags, p->ck.flag_words));
       LL_HIP(setup.launch(s));
       tend(p, s, LL_STAGE_LOOP_SETUP, ev);
       ll::CLoopArgs ca = c_common(p);
       ca.W = p->W[l];
       ca.woff = Il;
       ca.X = p->DZ;
-      ca.ring_ks = (int)(4L * H * p->es / 64);
+      ca.seq_len = p->seq_len;
       ca.c0 = p->c0 ? p->c0 + (long)l * B * H : nullptr;
       ca.stack = p->stack[l];
       ca.dy = l == L - 1 ? dy : p->dyc;
@@ -2037,7 +2033,7 @@ ll_status enqueue_bwd(ll_plan* p, hipStream_t s, const float* dy, const float* d
       ca.dh0 = dh0 ? dh0 + (long)l * B * H : nullptr;
       ca.dc0 = dc0 ? dc0 + (long)l * B * H : nullptr;
       ev = tbeg(p, s, LL_STAGE_BWD_LOOP);
-      LL_HIP(chained_loop_launch(p->device, s, [&] { return ll::c_launch(p->ck.bwd, ca, p->ck.lds_bwd, s); }));
+      LL_HIP(chained_loop_launch(p->device, s, [&] { return ll::c_launch(p->ck.bwd, ca, p->ck.lds, s); }));
       tend(p, s, LL_STAGE_BWD_LOOP, ev);
     }
     ll::BwdLoopArgs a{};
@@ -2257,6 +2253,11 @@ ll_status lstm_loop_fwd_noalloc(const ll_desc* desc, void* stream, const void* x
     return LL_OK;
   };
   st = plan_layout(&p, true, take);
+  if (st != LL_OK && p.cmode) {   // the exchange arrays do not fit: the grid-barrier loops need none
+    p.cmode = false;
+    used = 0;
+    st = plan_layout(&p, true, take);
+  }
   if (st != LL_OK) return st;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   // the device error word must start at zero (prep only ORs into it); the

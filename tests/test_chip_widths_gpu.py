@@ -1,0 +1,36 @@
+"""GPU parity of the chip-wide loops over their whole range: widths between
+the powers of two (odd counts of 32 units: shares of the reduction of unequal
+length, a last gradient column group that is half filled), and batches at the
+edges of the row groups (32) and of the waves' shares (64, 128, 256)."""
+import pytest
+
+from paper_1805_01772_amd import workloads as wl
+from _helpers import TOL, compare, oracle_reference, say
+from test_parity_gpu import run_case
+
+pytestmark = pytest.mark.gpu
+
+W = wl.Workload
+CASES = [W(f"chipw_{dtype}_b{B}_i{I}_h{H}_t{T}_l{L}", B=B, I=I, H=H, T_max=T, dtype=dtype, layers=L,
+           len_lo=0, len_hi=T, random_state=True, seed=seed)
+         for seed, (dtype, B, I, H, T, L) in enumerate([
+             ("bf16", 1, 8, 1056, 6, 1), ("bf16", 33, 24, 1184, 5, 1), ("bf16", 64, 16, 1536, 5, 1),
+             ("bf16", 65, 40, 1056, 5, 1), ("bf16", 128, 16, 2016, 4, 1), ("bf16", 129, 16, 1088, 5, 1),
+             ("bf16", 256, 8, 1280, 4, 2), ("f32", 1, 4, 544, 6, 1), ("f32", 40, 20, 672, 6, 1),
+             ("f32", 66, 12, 992, 4, 1), ("f32", 130, 8, 544, 5, 2), ("f32", 256, 8, 608, 4, 1)], start=301)]
+
+
+@pytest.mark.parametrize("w", CASES, ids=[w.name for w in CASES])
+def test_chip_widths_parity(w, monkeypatch):
+    monkeypatch.delenv("LSTMLOOP_LOOPS", raising=False)
+    say(f"[chip widths] {w.name}")
+    inp = wl.generate(w)
+    geom = {}
+    res, err = run_case(w, inp, geometry=geom)
+    assert geom["loops"] == "chip", geom
+    assert err == 0
+    ref = oracle_reference(inp, w.layers, w.dtype)
+    assert res["T_eff"] == ref["T_eff"]
+    errs, bad = compare(res, ref, TOL[w.dtype])
+    say(f"    errors {errs}")
+    assert not bad, bad
