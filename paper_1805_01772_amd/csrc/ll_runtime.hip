@@ -148,6 +148,7 @@ struct ll_plan {
   int dw_splits[2][3] = {{1, 1, 1}, {1, 1, 1}};   // split-K of each dW product (layer, part)
   bool xmode = false;          // XCD-local loops (ll_xloop.hip)
   ll::XKernels xk{};
+  bool xodd = false;           // rows of H operands are not 128-byte aligned (bf16, odd multiples of 32)
   int xP = 0;                  // unit blocks per XCD
   int xMRT = 0;                // row tiles per XCD
   int xhc = 0;                 // forward k-steps per wave
@@ -523,15 +524,21 @@ ll_status plan_configure(ll_plan* p, const ll_desc* desc, int device, const hipD
                 p->geom.nwg, occ_f, occ_b, p->n_cu);
   }
 
-  // XCD-local loops: 8 XCDs x 32 CUs, every exchanged row 128-byte aligned,
-  // H split 32 ways (bf16: 32 units per work-group, f32: 16).
+  // XCD-local loops: 8 XCDs x 32 CUs, H split 32 ways (bf16: 32 units per
+  // work-group, f32: 16).  The exchange moves whole k-step blocks, so any
+  // H % 32 fits; a bf16 width that is an odd number of 32 units (rows not
+  // 128-byte aligned) takes them for the LSTM body with its stack resident
+  // (training step of 60 steps, grid-barrier loops before and here: H = 96,
+  // B = 50 0.81 and 0.31 ms; H = 992, B = 512 7.15 and 1.88 ms); the other
+  // bodies and memory policies refuse it.
   const char* loops_env = getenv("LSTMLOOP_LOOPS");
   const bool allow = !(loops_env && strcmp(loops_env, "grid") == 0);
   {
     const int HJx = p->bf16 ? 32 : 16;
     const int P = H / HJx;
-    if (allow && p->n_cu == 256 && H % HJx == 0 && P >= 1 && P <= 32 &&
-        ((long)H * p->es) % 128 == 0) {
+    p->xodd = ((long)H * p->es) % 128 != 0;
+    const bool plain = desc->cell == LL_CELL_LSTM && !desc->spill && !desc->recompute;
+    if (allow && p->n_cu == 256 && H % HJx == 0 && P >= 1 && P <= 32 && (plain || !p->xodd)) {
       const int KS = p->bf16 ? H / 32 : H / 16;      // forward k-steps, 8 waves share them
       const int need = (KS + 7) / 8;
       const int hc = need <= 1 ? 1 : need <= 2 ? 2 : need <= 4 ? 4 : 0;
@@ -2253,8 +2260,8 @@ ll_status lstm_loop_fwd_noalloc(const ll_desc* desc, void* stream, const void* x
     return LL_OK;
   };
   st = plan_layout(&p, true, take);
-  if (st != LL_OK && p.cmode) {   // the exchange arrays do not fit: the grid-barrier loops need none
-    p.cmode = false;
+  if (st != LL_OK && (p.cmode || (p.xmode && p.xodd))) {   // the exchange arrays do not fit: the grid-barrier
+    p.cmode = p.xmode = p.wave = false;                     // loops need none
     used = 0;
     st = plan_layout(&p, true, take);
   }

@@ -1,10 +1,14 @@
-"""GPU parity of the chip-wide loops over their whole range: widths between
-the powers of two (odd counts of 32 units: shares of the reduction of unequal
+"""GPU parity of the loops at the widths between the powers of two.
+
+XCD-local loops: bfloat16 widths of an odd number of 32 units, one and two
+layers, one to four row tiles per XCD.  Chip-wide loops over their whole
+range: widths between the powers of two (odd counts of 32 units: shares of the reduction of unequal
 length, a last gradient column group that is half filled), and batches at the
 edges of the row groups (32) and of the waves' shares (64, 128, 256)."""
 import pytest
 
 from paper_1805_01772_amd import workloads as wl
+from paper_1805_01772_amd.lstmloop import LL_EUNSUPPORTED, LoopError, Plan
 from _helpers import TOL, compare, oracle_reference, say
 from test_parity_gpu import run_case
 
@@ -34,3 +38,34 @@ def test_chip_widths_parity(w, monkeypatch):
     errs, bad = compare(res, ref, TOL[w.dtype])
     say(f"    errors {errs}")
     assert not bad, bad
+
+
+ODD = [W(f"odd_bf16_b{B}_i{I}_h{H}_t{T}_l{L}", B=B, I=I, H=H, T_max=T, dtype="bf16", layers=L, len_lo=0,
+         len_hi=T, random_state=True, seed=seed)
+       for seed, (B, I, H, T, L) in enumerate([
+           (1, 8, 32, 9, 1), (17, 24, 96, 11, 1), (130, 16, 160, 7, 2), (300, 8, 288, 5, 1), (40, 40, 608, 6, 2),
+           (512, 8, 992, 3, 1)], start=331)]
+
+
+@pytest.mark.parametrize("w", ODD, ids=[w.name for w in ODD])
+def test_odd_widths_parity(w, monkeypatch):
+    monkeypatch.delenv("LSTMLOOP_LOOPS", raising=False)
+    say(f"[odd widths] {w.name}")
+    inp = wl.generate(w)
+    geom = {}
+    res, err = run_case(w, inp, geometry=geom)
+    assert geom["loops"] == "xcd", geom
+    assert err == 0
+    ref = oracle_reference(inp, w.layers, w.dtype)
+    assert res["T_eff"] == ref["T_eff"]
+    errs, bad = compare(res, ref, TOL[w.dtype])
+    say(f"    errors {errs}")
+    assert not bad, bad
+
+
+@pytest.mark.parametrize("kw", [dict(cell=1), dict(cell=2), dict(cell=3), dict(cell=4, ponder_max=2),
+                                dict(spill=1), dict(recompute=1)])
+def test_odd_widths_refused_for_other_bodies_and_policies(kw):
+    with pytest.raises(LoopError) as e:
+        Plan(8, 4, 32, 96, dtype="bf16", **kw)
+    assert e.value.status == LL_EUNSUPPORTED
