@@ -755,6 +755,10 @@ long gemm_rounds(const GemmArgs& g, int elem_bytes, int n_cu) {
     const long tiles = (long)((g.M + kBigTile - 1) / kBigTile) * ((g.N + kBigTile - 1) / kBigTile) * g.splits;
     return (tiles + n_cu - 1) / n_cu;
   }
+  if (elem_bytes == 4 && gemm32_nt_applies(g)) {   // (64x64 tiles, five work-groups per compute unit)
+    const long tiles = (long)((g.M + 63) / 64) * ((g.N + 63) / 64);
+    return (tiles + 5L * n_cu - 1) / (5L * n_cu);
+  }
   const long groups = (long)((g.M + 127) / 128) * ((g.N + 127) / 128) * g.splits;
   return (groups + 2L * n_cu - 1) / (2L * n_cu);
 }
@@ -772,6 +776,7 @@ hipError_t launch_gemm_nt(const GemmArgs& g, hipStream_t s) {
                        s, g, (unsigned)ab, (unsigned)bb);
     return hipGetLastError();
   }
+  if (sizeof(T) == 4 && gemm32_nt_applies(g)) return launch_gemm32_nt(g, s);
   if (g.pre_blocks > 0) {   // (the other kernels take no extra work-groups)
     const hipError_t e = launch_pre_jobs<T>(g.pre, s);
     if (e != hipSuccess) return e;

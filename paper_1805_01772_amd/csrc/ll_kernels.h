@@ -649,9 +649,19 @@ struct GemmTnArgs {
   unsigned* tile_flags;
   float* out;
   long ldo;
+  // float32 kernel: columns n >= n_from (a multiple of 64) of the C rows from
+  // M1 on take B's columns n + n_jump
+  int n_from, n_jump;
 };
 bool gemm_tn_applies(const GemmTnArgs& g);
 hipError_t launch_gemm_tn(const GemmTnArgs& g, hipStream_t s);
+// The same products in float32 (ll_gemm32.hip; launch_gemm_nt<float> takes
+// the NT one where it applies; M1 may be any multiple of 4 there).
+bool gemm32_nt_applies(const GemmArgs& g);
+hipError_t launch_gemm32_nt(const GemmArgs& g, hipStream_t s);
+bool gemm32_tn_applies(const GemmTnArgs& g);
+hipError_t launch_gemm32_tn(const GemmTnArgs& g, hipStream_t s);
+int gemm32_tn_splits(int M, int M1, int N, int n_from, long K, int n_cu);
 // Whether launch_gemm_nt takes the large-tile bf16 kernel for g, and how
 // many times the launch fills n_cu compute units (row capacity g.M).
 bool gemm_big_applies(const GemmArgs& g, int elem_bytes);

@@ -299,9 +299,14 @@ int dw_parts(const ll_plan* p, int l, DwPart* out) {
 // different arrays, so each is a product of its own; b_row is the dz column.
 // When the input width is a multiple of the 256-row tile the two parts of
 // one dz column range are one launch (m = Il + H; rows from Il on read the
-// h history).
+// h history).  The float32 kernel takes both parts in one launch always, the
+// GRU's candidate block included.
 int dw_parts_rows(const ll_plan* p, int l, DwPart* out) {
   const int H = p->d.H, Il = in_width(p, l);
+  if (!p->bf16) {
+    out[0] = DwPart{0, Il + H, 0, p->G * H, 0};
+    return 1;
+  }
   if (p->G == 3) {
     out[0] = DwPart{0, Il, 0, 3 * H, 0};
     out[1] = DwPart{Il, H, 0, 2 * H, 0};
@@ -649,9 +654,11 @@ ll_status plan_configure(ll_plan* p, const ll_desc* desc, int device, const hipD
     const double Il = in_width(p, l);
     const double flops = 2.0 * (Il + H) * p->G * H, bytes = (Il + H + p->GB * H) * 2.0 * p->es;
     const long lim = 1L << 31;
-    const bool fits = p->cap * (long)Il * 2 < lim && (p->cap + B) * (long)H * 2 < lim &&
-                      p->cap * (long)p->GB * H * 2 < lim;
-    p->dw_rows[l] = p->bf16 && fits && flops / bytes < 1170.0;
+    const bool fits = p->cap * (long)Il * p->es < lim && (p->cap + B) * (long)H * p->es < lim &&
+                      p->cap * (long)p->GB * H * p->es < lim;
+    // (float32: the product over rows runs at the matrix cores' rate, as one
+    // on transposed copies would)
+    p->dw_rows[l] = fits && (!p->bf16 || flops / bytes < 1170.0);
   }
   for (int l = 0; l < L; ++l) {   // the products over rows
     if (!p->dw_rows[l]) continue;
@@ -662,9 +669,11 @@ ll_status plan_configure(ll_plan* p, const ll_desc* desc, int device, const hipD
                          ((parts[k].n + ll::kGemmBigTile - 1) / ll::kGemmBigTile);
       long sp = (p->n_cu + tiles - 1) / tiles;
       sp = std::max(1L, std::min(16L, std::min(sp, std::max(1L, p->cap / 256))));
+      if (!p->bf16)
+        sp = ll::gemm32_tn_splits(parts[k].m, in_width(p, l), parts[k].n, p->G == 3 ? 2 * H : 0, p->cap, p->n_cu);
       p->tn_splits[l][k] = (int)sp;
       if (sp > 1) p->ws_floats = std::max(p->ws_floats, sp * parts[k].m * parts[k].n);
-      if (sp == 2) p->tn_flag_words = std::max(p->tn_flag_words, 2 * tiles);
+      if (p->bf16 && sp == 2) p->tn_flag_words = std::max(p->tn_flag_words, 2 * tiles);
     }
   }
   for (int l = 0; l < L; ++l) {
@@ -1384,6 +1393,16 @@ ll_status enqueue_fwd(ll_plan* p, hipStream_t s, const void* x, const int32_t* s
   return LL_OK;
 }
 
+// The product over rows of the operand type.
+template <typename T>
+bool tn_applies(const ll::GemmTnArgs& g) {
+  return sizeof(T) == 2 ? ll::gemm_tn_applies(g) : ll::gemm32_tn_applies(g);
+}
+template <typename T>
+hipError_t launch_tn(const ll::GemmTnArgs& g, hipStream_t s) {
+  return sizeof(T) == 2 ? ll::launch_gemm_tn(g, s) : ll::launch_gemm32_tn(g, s);
+}
+
 // Products after the gradient loop of layer l: db from the loop's row-group
 // partials, dW = [x_t, h_{t-1}]^T dz_t summed over steps, and, if dx is not
 // NULL, dx_t = dz_t W_x^T (layer 0: time-major [T_max, B, I]; layer 1:
@@ -1502,27 +1521,31 @@ ll_status bwd_products(ll_plan* p, hipStream_t s, int l, const void* dz, const f
       g.splits = p->tn_splits[l][k];
       // (the plan chose this path only for operands below 2^31 bytes, and
       // lstm_loop_fwd accepted only a 16-byte aligned x)
-      if (!ll::gemm_tn_applies(g))
+      if (!p->bf16 && p->G == 3) {   // the candidate block's recurrent side: dz columns 3H ..
+        g.n_from = 2 * H;
+        g.n_jump = H;
+      }
+      if (!tn_applies<T>(g))
         return fail(LL_EHIP, "internal: the dW product over rows does not apply to layer %d", l);
       float* out = dW[l] + (long)q.a_row * GH + q.c_col;
-      if (g.splits == 2 && p->tn_flags) {   // the two splits sum in place
+      if (g.splits == 2 && p->bf16 && p->tn_flags) {   // the two splits sum in place
         g.C = p->ws;
         g.ldc = q.n;
         g.split_stride = (long)q.m * q.n;
         g.tile_flags = p->tn_flags;
         g.out = out;
         g.ldo = GH;
-        LL_HIP(ll::launch_gemm_tn(g, s));
+        LL_HIP(launch_tn<T>(g, s));
       } else if (g.splits > 1) {
         g.C = p->ws;
         g.ldc = q.n;
         g.split_stride = (long)q.m * q.n;
-        LL_HIP(ll::launch_gemm_tn(g, s));
+        LL_HIP(launch_tn<T>(g, s));
         LL_HIP(ll::launch_sum_slices_2d(p->ws, g.splits, g.split_stride, q.m, q.n, out, GH, s));
       } else {
         g.C = out;
         g.ldc = GH;
-        LL_HIP(ll::launch_gemm_tn(g, s));
+        LL_HIP(launch_tn<T>(g, s));
       }
     }
   } else {
@@ -1663,9 +1686,9 @@ ll_status act_products(ll_plan* p, hipStream_t s, float* dx, float* const* dW, f
         g.C = p->ws + (long)k * sp * pt.m * pt.n;
         g.ldc = pt.n;
         g.split_stride = (long)pt.m * pt.n;
-        if (!ll::gemm_tn_applies(g))
+        if (!tn_applies<T>(g))
           return fail(LL_EHIP, "internal: the dW product over rows does not apply (ponder slot %d)", k);
-        LL_HIP(ll::launch_gemm_tn(g, s));
+        LL_HIP(launch_tn<T>(g, s));
       }
       LL_HIP(ll::launch_sum_slices_2d(p->ws, M * sp, (long)pt.m * pt.n, pt.m, pt.n,
                                       dW[0] + (long)pt.a_row * GH + pt.c_col, GH, s));
