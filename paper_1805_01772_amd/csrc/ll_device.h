@@ -78,6 +78,12 @@ __device__ __forceinline__ float tanhf_(float u) {
   return __builtin_fabsf(u) < 0.125f ? small : big;
 }
 
+// c_t = f c_{t-1} + i g with the rounding pinned (one product rounded, one
+// fused), so that every kernel that computes it gets the same bits.
+__device__ __forceinline__ float lstm_c(float i, float f, float g, float c) {
+  return __builtin_fmaf(f, c, __fmul_rn(i, g));
+}
+
 __device__ __forceinline__ uint4 zero4() { return make_uint4(0u, 0u, 0u, 0u); }
 
 __device__ __forceinline__ uint4 ld16(const void* p) {

@@ -307,11 +307,12 @@ struct XLoopArgs {
   unsigned* dyx_flags;    // gradient: per-member flags of dyx_ring ([8][MRT][32])
   const unsigned* peer_flags;  // gradient: the other layer's step flags
   const void* Wx;         // upper layer, gradient: W rows of the input part [I_l, 4H]
-  // saved values: the c field of row (t, r) at stack + stack_row(t, r) * sld
-  // + scoff; i, f, g, o at gstk + grow(t, r) * gld + {0, H, 2H, 3H}, where
+  // saved values: c of row (t, r) at cstk + stack_row(t, r) * csld; i, f, g,
+  // o at gstk + grow(t, r) * gld + {0, H, 2H, 3H}, where
   // grow maps like stack_row with gchunk / gslots (gstk NULL: the gates sit
-  // in the stack rows, those of unit u at 4u .. 4u+3)
-  int sld, scoff;
+  // in the stack rows, stack + stack_row * sld, those of unit u at 4u .. 4u+3)
+  int sld, csld;
+  float* cstk;
   int sgates;             // forward: 1 = push i, f, g, o with c (0: c only); the
                           // GRU pushes r, u, n, zh_n + b_hn and h_{t-1} in their places
   const float* gstk;
@@ -422,6 +423,12 @@ hipError_t launch_copy_i32(const int* src, int* dst, int n, hipStream_t s);
 hipError_t launch_sum_scatter_rows(const float* ws, int nsl, long stride, const int* meta, const int* rowmap,
                                    int C, float* out, long cap_rows, hipStream_t s);
 hipError_t launch_zero_u32(unsigned* p, int n, hipStream_t s);
+// c of steps [t0, t1) rebuilt from the gates (rows (t - t0) B + r of `gates`
+// [.., 4H], unit u's i, f, g, o at 4u) and the entering state c_in [B, H]
+// (original order, or NULL), into rows (t - t0) B + r of c [.., H]: the same
+// operations as the forward loop's, so the same bits.
+hipError_t launch_rebuild_c(const float* gates, const float* c_in, const int* active, const int* perm, int B, int H,
+                            int t0, int t1, float* c, hipStream_t s);
 
 // Sustained matrix-core rate of the device (TFLOP/s), for reports: the 16x16
 // k-step the loops use, or the 32x32 shape.

@@ -219,6 +219,7 @@ struct ll_plan {
   // ... and W_h in unit-major order and, with xflags_b, the gradient loop's flags
   bool bwd_prepared = false;
   std::vector<hipEvent_t> ev_d2h, ev_h2d;   // per (layer, slot)
+  float* c_enter = nullptr;    // spill: c entering each chunk, [layers][nchunks][B, H] (original order)
   float* carry = nullptr;      // [4][B, H]: h, c (forward) / dh, dc (backward) between chunks
   float* db_state = nullptr;   // per-thread db sums between backward chunks
   float* db_part = nullptr;
@@ -377,7 +378,7 @@ void free_plan_memory(ll_plan* p) {
                   p->dyc, p->xring, p->xflags, p->db_part, p->ws, p->carry, p->db_state,
                   p->xring2, p->DZ2, p->dyx, p->db_part2, p->cring, p->cpart, p->cflags,
                   p->gslot, p->rc_inmap, p->rc_prevmap, p->rc_bias, p->sx, p->guards, p->Wum[0],
-                  p->Wum[1], p->prevc, p->HI, p->ntrip, p->tn_flags, p->xflags_b};
+                  p->Wum[1], p->prevc, p->HI, p->ntrip, p->tn_flags, p->xflags_b, p->c_enter};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   for (float* h : p->host_stack)
@@ -792,6 +793,7 @@ ll_status plan_layout(ll_plan* p, bool fwd_only, Take&& take) {
     ALLOC(p->rc_prevmap, sizeof(int) * cap, "recomputation row maps");
     ALLOC(p->rc_bias, sizeof(float) * L * 4 * H, "saved bias");
   }
+  if (p->spill) ALLOC(p->c_enter, sizeof(float) * L * (long)p->nchunks * B * H, "chunk entering states");
   if (p->spill || p->recompute) {
     ALLOC(p->carry, sizeof(float) * 4 * B * H, "chunk carry");
     ALLOC(p->db_state, sizeof(float) * 8 * 32 * 512 * 4, "db state");
@@ -945,7 +947,9 @@ ll_status ll_plan_create(const ll_desc* desc, int device, ll_plan** out) {
   }
   const int64_t stack_dev = p->spill ? (int64_t)sizeof(float) * p->nslots * p->slot_floats
                                      : (int64_t)sizeof(float) * p->M * cap * (p->recompute || p->G == 1 ? 1 : 5) * H;
-  p->stack_device_bytes = (int64_t)L * (stack_dev + (int64_t)es * (cap + (p->recompute ? B : 0)) * H);
+  // (the swapped chunks' c is rebuilt from c entering each chunk: 4/5 of the
+  // bytes cross the host link)
+  p->stack_device_bytes = (p->spill ? (int64_t)sizeof(float) * L * p->nchunks * B * H : 0) + (int64_t)L * (stack_dev + (int64_t)es * (cap + (p->recompute ? B : 0)) * H);
   if (p->recompute) p->stack_device_bytes += (int64_t)sizeof(float) * p->rc_steps * B * 4 * H;
   p->stack_host_bytes =
       p->spill ? (int64_t)L * (int64_t)sizeof(float) * std::max(0, p->nchunks - p->nslots) * p->slot_floats : 0;
@@ -1066,10 +1070,23 @@ ll::XLoopArgs x_common(const ll_plan* p) {
   // 4u .. 4u+3, then c_t); GRU r, u, n, zh_n + b_hn, h_{t-1} (the same
   // layout); the RNN pushes h_t only
   const bool five = p->G == 4 || p->G == 3;
-  a.sld = five ? 5 * p->d.H : p->d.H;
-  a.scoff = five ? 4 * p->d.H : 0;
+  a.sld = a.csld = five ? 5 * p->d.H : p->d.H;
   a.sgates = five ? 1 : 0;
+  if (p->spill) {            // ring of chunk slots: the gates of every slot, then c of every slot
+    a.sld = 4 * p->d.H;
+    a.csld = p->d.H;
+  } else if (p->recompute) { // c only
+    a.sld = a.csld = p->d.H;
+    a.sgates = 0;
+  }
   return a;
+}
+
+// c of the saved stack (see x_common).
+float* c_of_stack(const ll_plan* p, float* stack) {
+  if (!stack) return nullptr;
+  if (p->spill) return stack + (long)p->nslots * p->chunk_steps * p->d.B * 4 * p->d.H;
+  return stack + (p->recompute || p->G == 1 ? 0 : 4 * p->d.H);
 }
 
 // Two-layer wavefront, forward: the input projection of layer 0 only (the
@@ -1121,6 +1138,7 @@ ll_status enqueue_fwd_wave(ll_plan* p, hipStream_t s, const void* x, const void*
   a0.X = p->HH[0];
   a0.Zx = p->Zx;
   a0.stack = save ? p->stack[0] : nullptr;
+  a0.cstk = c_of_stack(p, a0.stack);
   a0.h0 = h0;
   a0.c0 = c0;
   a0.hT = hT;
@@ -1136,6 +1154,7 @@ ll_status enqueue_fwd_wave(ll_plan* p, hipStream_t s, const void* x, const void*
   a1.X = p->HH[1];
   a1.zbias = bias[1];
   a1.stack = save ? p->stack[1] : nullptr;
+  a1.cstk = c_of_stack(p, a1.stack);
   a1.y = y;
   a1.h0 = h0 ? h0 + BH : nullptr;
   a1.c0 = c0 ? c0 + BH : nullptr;
@@ -1242,9 +1261,6 @@ ll_status enqueue_fwd(ll_plan* p, hipStream_t s, const void* x, const int32_t* s
       const int ring_ks = (int)((long)H * p->es / 64);
       ll::XLoopArgs xa = x_common(p);
       if (p->recompute) {   // push c_t only; keep the bias for the gate recomputation
-        xa.sld = H;
-        xa.scoff = 0;
-        xa.sgates = 0;
         if (save)
           LL_HIP(hipMemcpyAsync(p->rc_bias + (long)l * 4 * H, bias[l], sizeof(float) * 4 * H,
                                 hipMemcpyDeviceToDevice, s));
@@ -1284,6 +1300,7 @@ ll_status enqueue_fwd(ll_plan* p, hipStream_t s, const void* x, const int32_t* s
         xa.HI = p->HI;
       }
       xa.stack = save ? p->stack[l] : nullptr;
+      xa.cstk = c_of_stack(p, xa.stack);
       xa.y = (l == L - 1) ? y : nullptr;
       xa.abort_flag = p->meta + 3;
       xa.err = p->meta + 2;
@@ -1319,7 +1336,10 @@ ll_status enqueue_fwd(ll_plan* p, hipStream_t s, const void* x, const int32_t* s
         xa.h0 = hin;
         xa.c0 = cin;
         xa.hT = last ? hout : p->carry;
-        xa.cT = last ? cout : p->carry + (long)B * H;
+        // (spill: c entering the next chunk stays, the swapped-in chunks'
+        // c is rebuilt from it)
+        float* const cnext = p->spill ? p->c_enter + ((long)l * nch + k + 1) * B * H : p->carry + (long)B * H;
+        xa.cT = last ? cout : cnext;
         LL_HIP(chained_loop_launch(p->device, s, [&] { return ll::x_launch(p->xk.fwd, xa, 256, p->xk.lds_fwd, s); }));
         tend(p, s, LL_STAGE_FWD_LOOP, ev);
         if (p->spill && save && k < nch - p->nslots) {   // evicted later: swap it out on the copy stream
@@ -1327,13 +1347,13 @@ ll_status enqueue_fwd(ll_plan* p, hipStream_t s, const void* x, const int32_t* s
           // (two copy streams: the next chunk's copy is queued while this one runs)
           hipStream_t cs = (k & 1) ? p->cstream2 : p->cstream;
           LL_HIP(hipStreamWaitEvent(cs, p->ev_compute, 0));
-          LL_HIP(copy_on_dma_engine(p->host_stack[l] + (long)k * p->slot_floats,
-                                    p->stack[l] + (long)slot * p->slot_floats, sizeof(float) * p->slot_floats,
-                                    hipMemcpyDeviceToHost, cs));
+          const long gate_floats = (long)C * B * 4 * H;   // (c is rebuilt, not moved)
+          LL_HIP(copy_on_dma_engine(p->host_stack[l] + (long)k * p->slot_floats, p->stack[l] + slot * gate_floats,
+                                    sizeof(float) * gate_floats, hipMemcpyDeviceToHost, cs));
           LL_HIP(hipEventRecord(p->ev_d2h[l * p->nslots + slot], cs));
         }
         hin = p->carry;
-        cin = p->carry + (long)B * H;
+        cin = cnext;
       }
       continue;
     }
@@ -1816,6 +1836,7 @@ ll_status enqueue_bwd_wave(ll_plan* p, hipStream_t s, const float* dy, const flo
   a0.X = p->DZ;
   a0.c0 = p->c0;
   a0.stack = p->stack[0];
+  a0.cstk = c_of_stack(p, a0.stack);
   a0.dhT = dhT;
   a0.dcT = dcT;
   a0.db_part = p->db_part;
@@ -1833,6 +1854,7 @@ ll_status enqueue_bwd_wave(ll_plan* p, hipStream_t s, const float* dy, const flo
   a1.X = p->DZ2;
   a1.c0 = p->c0 ? p->c0 + BH : nullptr;
   a1.stack = p->stack[1];
+  a1.cstk = c_of_stack(p, a1.stack);
   a1.dy = dy;
   a1.dy_compact = 0;
   a1.dhT = dhT ? dhT + BH : nullptr;
@@ -1967,6 +1989,7 @@ ll_status enqueue_bwd(ll_plan* p, hipStream_t s, const float* dy, const float* d
       }
       xa.c0 = p->c0 && p->G == 4 ? p->c0 + (long)l * B * H : nullptr;
       xa.stack = p->stack[l];
+      xa.cstk = c_of_stack(p, xa.stack);
       xa.guard = p->skip ? p->guards + (long)l * p->cap : p->act ? p->guards : nullptr;
       if (p->act) {
         xa.ponder_max = p->M;
@@ -1995,8 +2018,6 @@ ll_status enqueue_bwd(ll_plan* p, hipStream_t s, const float* dy, const float* d
       xa.nslots = R;
       xa.db_state = (p->spill || p->recompute) ? p->db_state : nullptr;
       if (p->recompute) {   // c_t from the c-only stack, the gates from the chunk buffer
-        xa.sld = H;
-        xa.scoff = 0;
         xa.gstk = p->gslot;
         xa.gld = 4 * H;
         xa.gchunk = C;
@@ -2005,18 +2026,23 @@ ll_status enqueue_bwd(ll_plan* p, hipStream_t s, const float* dy, const float* d
       }
       // chunks at or above nch - R are still in the ring after the forward; a
       // chunk j below is swapped in after the launch of chunk j + R (the last
-      // use of its slot) and waited for before the launches of j + 1 (which
-      // reads c_{t-1} from it) and j
-      auto wait_loaded = [&](int j) -> hipError_t {
-        if (!p->spill || j < 0 || j >= nch - R) return hipSuccess;
-        return hipStreamWaitEvent(s, p->ev_h2d[l * R + j % R], 0);
+      // use of its slot) and waited for, its c rebuilt, before the launches of
+      // j + 1 (which reads c_{t-1} from it) and j
+      auto load_chunk = [&](int j) -> ll_status {
+        if (!p->spill || j < 0 || j >= nch - R) return LL_OK;
+        LL_HIP(hipStreamWaitEvent(s, p->ev_h2d[l * R + j % R], 0));
+        const float* cin = j > 0 ? p->c_enter + ((long)l * nch + j) * B * H : xa.c0;
+        const long rows = (long)C * B;
+        LL_HIP(ll::launch_rebuild_c(p->stack[l] + (j % R) * rows * 4 * H, cin, p->active, p->perm, B, H, j * C,
+                                    std::min(d.T_max, (j + 1) * C), xa.cstk + (j % R) * rows * H, s));
+        return LL_OK;
       };
       for (int k = nch - 1; k >= 0; --k) {
         const int t0 = k * C, t1 = std::min(d.T_max, t0 + C);
         const bool first = k == nch - 1, last = k == 0;
         ev = tbeg(p, s, LL_STAGE_LOOP_SETUP);
-        LL_HIP(wait_loaded(k));
-        LL_HIP(wait_loaded(k - 1));
+        // (chunk k itself was waited for, and its c rebuilt, before the launch of k + 1)
+        LL_STATUS(load_chunk(k - 1));
         if (fl == p->xflags) LL_HIP(setup.zero_u32(p->xflags, p->xflag_words));
         LL_HIP(setup.launch(s));   // (nothing left: no launch)
         tend(p, s, LL_STAGE_LOOP_SETUP, ev);
@@ -2036,9 +2062,9 @@ ll_status enqueue_bwd(ll_plan* p, hipStream_t s, const float* dy, const float* d
           LL_HIP(hipEventRecord(p->ev_compute, s));
           hipStream_t cs = (j & 1) ? p->cstream2 : p->cstream;
           LL_HIP(hipStreamWaitEvent(cs, p->ev_compute, 0));
-          LL_HIP(copy_on_dma_engine(p->stack[l] + (long)(j % R) * p->slot_floats,
-                                    p->host_stack[l] + (long)j * p->slot_floats, sizeof(float) * p->slot_floats,
-                                    hipMemcpyHostToDevice, cs));
+          const long gate_floats = (long)C * B * 4 * H;
+          LL_HIP(copy_on_dma_engine(p->stack[l] + (j % R) * gate_floats, p->host_stack[l] + (long)j * p->slot_floats,
+                                    sizeof(float) * gate_floats, hipMemcpyHostToDevice, cs));
           LL_HIP(hipEventRecord(p->ev_h2d[l * R + j % R], cs));
         }
       }

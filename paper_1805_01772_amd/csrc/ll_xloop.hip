@@ -417,7 +417,7 @@ __device__ __forceinline__ void xfwd_body(const XLoopArgs& a, int grp, int rank,
           fg = sigmoidf_(z[1]);
           gg = tanhf_(z[2]);
           og = sigmoidf_(z[3]);
-          cn = fg * cs[mt] + ig * gg;
+          cn = lstm_c(ig, fg, gg, cs[mt]);
           hn = og * tanhf_(cn);
           if ((SKIP || ACT) && !run) {   // the false branch / a halted row keeps the state
             cn = cs[mt];
@@ -449,7 +449,7 @@ __device__ __forceinline__ void xfwd_body(const XLoopArgs& a, int grp, int rank,
           const long vr = (long)k * a.slot_rows + off_t + r;
           float* srow = a.stack + vr * a.sld;
           *reinterpret_cast<float4*>(srow + 4 * ju) = make_float4(ig, fg, gg, og);
-          srow[a.scoff + ju] = cn;
+          a.cstk[vr * a.csld + ju] = cn;
           reinterpret_cast<T*>(a.HI)[vr * H + ju] = Op<T>::from_f32(hn);
           if (rank == 0 && cu == 0) a.guard[vr] = run ? 1.f : 0.f;
         }
@@ -459,15 +459,15 @@ __device__ __forceinline__ void xfwd_body(const XLoopArgs& a, int grp, int rank,
         const long cr = off_t + r;
         HH[cr * H + ju] = Op<T>::from_f32(hn);
         if (a.stack) {
-          float* srow = a.stack + stack_row(a, t, r) * a.sld;
+          const long sr = stack_row(a, t, r);
           if constexpr (G == 4 || G == 3) {
             // the unit's four gate values side by side (stack row: 4H gate
-            // values unit by unit, then c): one 16-byte store
-            if (a.sgates) *reinterpret_cast<float4*>(srow + 4 * ju) = make_float4(ig, fg, gg, og);
-            srow[a.scoff + ju] = cn;
+            // values unit by unit): one 16-byte store
+            if (a.sgates) *reinterpret_cast<float4*>(a.stack + sr * a.sld + 4 * ju) = make_float4(ig, fg, gg, og);
+            a.cstk[sr * a.csld + ju] = cn;
             if (SKIP && rank == 0 && cu == 0) a.guard[cr] = run ? 1.f : 0.f;
           } else {
-            srow[a.scoff + ju] = hn;   // the RNN's gradient needs only h_t
+            a.cstk[sr * a.csld + ju] = hn;   // the RNN's gradient needs only h_t
           }
         }
       }
@@ -669,10 +669,9 @@ __device__ __forceinline__ void xbwd_body(const XLoopArgs& a, int grp, int rank,
     const bool ok = cellt && crow < nr;
     const int b = sperm[mt * 16 + crow];
     const int ts = max(tt, 0);
-    const long SL = a.sld, GL = a.gstk ? a.gld : a.sld;
+    const long SL = a.csld, GL = a.gstk ? a.gld : a.sld;
     const unsigned so = ok ? (unsigned)((crow * SL + ju) * 4) : kOOB;
-    const __amdgpu_buffer_rsrc_t rs =
-        make_rsrc(a.stack + stack_row(a, ts, r0) * SL + a.scoff, (unsigned)(nr * SL * 4));
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(a.cstk + stack_row(a, ts, r0) * SL, (unsigned)(nr * SL * 4));
     if constexpr (G == 1) {   // RNN: h_t and dy
       v[0] = ld_f32(rs, so);
       v[1] = v[2] = v[3] = v[4] = v[5] = 0.f;
@@ -696,7 +695,7 @@ __device__ __forceinline__ void xbwd_body(const XLoopArgs& a, int grp, int rank,
       v[5] = 0.f;
     } else if (tt > 0) {
       const __amdgpu_buffer_rsrc_t rp2 =
-          make_rsrc(a.stack + stack_row(a, tt - 1, r0) * SL + a.scoff, (unsigned)(nr * SL * 4));
+          make_rsrc(a.cstk + stack_row(a, tt - 1, r0) * SL, (unsigned)(nr * SL * 4));
       v[5] = ld_f32(rp2, so);
     } else {
       const __amdgpu_buffer_rsrc_t rc = make_rsrc(a.c0, a.c0 ? (unsigned)(B * H * 4) : 0u);
@@ -731,21 +730,22 @@ __device__ __forceinline__ void xbwd_body(const XLoopArgs& a, int grp, int rank,
     const long SL = a.sld;
     const long vr = (long)max(kk, 0) * a.slot_rows + off + r0;     // first row of the tile's slot
     const __amdgpu_buffer_rsrc_t rg = make_rsrc(a.stack + vr * SL, (unsigned)(nr * SL * 4));
-    const unsigned go = ok ? (unsigned)((crow * SL + ju) * 4) : kOOB;
     const float4 g4 = ld_f32x4(rg, ok ? (unsigned)((crow * SL + 4 * ju) * 4) : kOOB);
     v[0] = g4.x;
     v[1] = g4.y;
     v[2] = g4.z;
     v[3] = g4.w;
-    v[4] = ld_f32(rg, go + a.scoff * 4);
+    const long CL = a.csld;
+    const __amdgpu_buffer_rsrc_t rcs = make_rsrc(a.cstk + vr * CL, (unsigned)(nr * CL * 4));
+    const unsigned co = ok ? (unsigned)((crow * CL + ju) * 4) : kOOB;
+    v[4] = ld_f32(rcs, co);
     if (kk > 0) {
-      const __amdgpu_buffer_rsrc_t rp2 =
-          make_rsrc(a.stack + (vr - a.slot_rows) * SL, (unsigned)(nr * SL * 4));
-      v[5] = ld_f32(rp2, go + a.scoff * 4);
+      const __amdgpu_buffer_rsrc_t rp2 = make_rsrc(a.cstk + (vr - a.slot_rows) * CL, (unsigned)(nr * CL * 4));
+      v[5] = ld_f32(rp2, co);
     } else if (tt > 0) {
       const long pr = (long)(np_prev - 1) * a.slot_rows + offp + r0;
-      const __amdgpu_buffer_rsrc_t rp2 = make_rsrc(a.stack + pr * SL, (unsigned)(nr * SL * 4));
-      v[5] = ld_f32(rp2, go + a.scoff * 4);
+      const __amdgpu_buffer_rsrc_t rp2 = make_rsrc(a.cstk + pr * CL, (unsigned)(nr * CL * 4));
+      v[5] = ld_f32(rp2, co);
     } else {
       const __amdgpu_buffer_rsrc_t rc = make_rsrc(a.c0, a.c0 ? (unsigned)(B * H * 4) : 0u);
       v[5] = ld_f32(rc, ok ? (unsigned)((b * H + ju) * 4) : kOOB);

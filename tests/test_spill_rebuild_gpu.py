@@ -1,0 +1,38 @@
+"""GPU test of the c values rebuilt for swapped-in chunks: a swapped stack
+gives the resident stack's results bitwise at the edges of the chunks (a
+chunk of one step, a last chunk cut short, rows that end on a chunk's first
+and last step, rows that never start, random entering states in two layers)."""
+import numpy as np
+import pytest
+
+from paper_1805_01772_amd import workloads as wl
+from paper_1805_01772_amd.runner import DeviceCase
+from _helpers import say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,layers,B,H,T,C", [("f32", 1, 17, 64, 13, 1), ("f32", 2, 20, 32, 31, 4),
+                                                  ("bf16", 1, 33, 64, 24, 6), ("bf16", 1, 130, 128, 22, 3)])
+def test_swapped_stack_bitwise_at_chunk_edges(dtype, layers, B, H, T, C, monkeypatch):
+    monkeypatch.setenv("LSTMLOOP_WAVEFRONT", "off")
+    w = wl.Workload("rebuild", B=B, I=24, H=H, T_max=T, dtype=dtype, layers=layers, len_lo=0, len_hi=T,
+                    w_scale=0.3, random_state=True, seed=77)
+    inp = wl.generate(w)
+    edges = [0, 1, C, C + 1, 2 * C, 3 * C, T - 1, T]
+    inp["seq_len"][:len(edges)] = np.minimum(edges, T)
+    say(f"[spill] rebuilt c, {dtype}, {layers} layer(s), B={B} H={H} T={T} chunks of {C}")
+    outs = []
+    for kw in ({}, dict(spill=1, spill_chunk_steps=C, device_stack_budget_bytes=1)):
+        dc = DeviceCase(inp, H, 24, layers, dtype)
+        plan = dc.plan(**kw)
+        for _ in range(2):
+            dc.fwd(plan)
+            dc.bwd(plan)
+        assert plan.status_sync() == 0
+        outs.append(dc.results())
+        plan.close()
+    for k in ("y", "hT", "cT", "dx", "dh0", "dc0"):
+        np.testing.assert_array_equal(outs[0][k], outs[1][k])
+    for a, b in zip(outs[0]["dW"] + outs[0]["dbias"], outs[1]["dW"] + outs[1]["dbias"]):
+        np.testing.assert_array_equal(a, b)
