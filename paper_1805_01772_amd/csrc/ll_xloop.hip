@@ -240,6 +240,8 @@ __device__ __forceinline__ void xfwd_body(const XLoopArgs& a, int grp, int rank,
 
   const int T_eff = uni(a.meta[0]);
   const int t0 = a.t_begin, t1 = min(a.t_end, T_eff);
+  // a launch stays within one chunk: its stack rows are (srow0 + t) B + r
+  const int srow0 = uni((t0 / a.chunk_steps) % a.nslots * a.chunk_steps - t0 / a.chunk_steps * a.chunk_steps);
   int wlo = t0 > 0 ? t0 - 1 : 0;
   load_window(a, win, wlo);
   // input projections of the cell thread's (row, unit), one step ahead (the
@@ -459,7 +461,7 @@ __device__ __forceinline__ void xfwd_body(const XLoopArgs& a, int grp, int rank,
         const long cr = off_t + r;
         HH[cr * H + ju] = Op<T>::from_f32(hn);
         if (a.stack) {
-          const long sr = stack_row(a, t, r);
+          const long sr = (long)(srow0 + t) * B + r;
           if constexpr (G == 4 || G == 3) {
             // the unit's four gate values side by side (stack row: 4H gate
             // values unit by unit): one 16-byte store
