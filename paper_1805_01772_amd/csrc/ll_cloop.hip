@@ -4,58 +4,71 @@
 // loop, split over the work-groups of the chip, and the loop state crosses
 // XCDs every step.
 //
-// Work split.  The output columns of the recurrent product are cut into
-// groups of 64 (forward: the four gates of 16 units; gradient: 64 units) and
-// the reduction into KG slices; work-group (group, slice) holds a slice of H/32
+// Forward split.  A work-group takes the gate columns of KPC hidden units (8
+// bf16, 4 f32) over the whole reduction, so nothing but h_t crosses
+// work-groups: it streams all of h_{t-1} and its product needs no partner.
+// Gradient split.  The reduction is four times as long there (K = 4H), so the
+// output columns are cut into groups of 64 units and the reduction into KG
+// slices (8 bf16, 16 f32); work-group (group, slice) holds a slice of H/32
 // k-steps x 64 columns (64 H bytes of LDS) and runs the cell of CW of the
 // group's units.  A group's KG work-groups sit on one XCD.
-//   forward:  z = h_{t-1} W_h, K = H,  KG = 2 (bf16) / 4 (f32)
-//   gradient: dh_{t-1} = dz_t W_h^T, K = 4H, KG = 8 / 16
 //
 // Inside a work-group every wave runs the recurrence of its own rows alone:
 // the batch is cut into groups of 32 rows, wave w takes row group w % RW and
-// share w / RW of the work-group's reduction slice (RW KW = 8: KW = 1 for
-// more than 128 rows, 2 for more than 64, else 4, so that a small batch still
-// spreads over the waves).  No barrier and no sum over waves stands in
-// a step: the shares meet as partial products of the group, like the KG
-// slices, and the waves of a SIMD hide each other's waits.  (The form this
-// replaced kept the weights in registers, split the reduction over the eight
-// waves of a work-group, and so summed eight partials through LDS behind a
-// barrier for every 16 rows; it took only H = 2048 / 1024, other widths ran on
-// the grid-barrier loops.  Training step, before and after: two layers of bf16
-// H = 2048 at B = 256 19.5 -> 17.7 ms; bf16 H = 1536, B = 72, 90 steps 6.2 ->
-// 1.9 ms; f32 H = 640 inference, B = 50, 73 steps 1.53 -> 1.00 ms.)
+// share w / RW of the work-group's reduction (RW KW = 8: KW = 1 for more than
+// 128 rows, 2 for more than 64, 4 below, and 8 forward for at most 32, so
+// that a small batch still spreads over the waves).  No barrier stands in a
+// step: the shares meet in LDS behind flags (forward) or as partial products
+// of the group, like the KG slices (gradient), and the waves of a SIMD hide
+// each other's waits.  Measured: the forward loop with a reduction split over
+// KG = 2 / 4 work-groups and their partial products in the L2 took, per step,
+// bf16 H = 2048 18.0 us (B = 64), 23.9 (128), 32.1 (256), H = 1536 15.7 (64),
+// 19.1 (128), f32 H = 640 16.4 (64), 15.2 (128); with the whole reduction per
+// work-group 11.7, 14.3, 31.3, 10.0, 11.3, 11.2, 11.8.  Above 128 rows the
+// 1 MB that every work-group then streams evens the two out (B = 160 to 192
+// of bf16 H = 2048 and 256 of f32 H = 1024 are 4-7 % slower than split, the
+// narrower widths 4-16 % faster).
 //
-// One step of a wave (forward; the gradient loop runs its cell first):
-//   phase A: wait for the producers of its k-steps of h_{t-1}, stream them
-//     from the exchange ring (device-scope loads, 8 to 16 k-steps in flight)
-//     against the weights in LDS (32x32 MFMAs), store the 32 x 64 partial
-//     product into the XCD's L2 and set the wave's partial flag;
-//   phase B: wait for the KG KW partial products of its column group, sum
-//     them for its share of the cells, add the input projection, run the
-//     cell, store h_t into the ring with device-scope stores (written through
-//     to where every XCD's loads see it), set the wave's exchange flag; then
-//     the h history, stack and y.
+// One step of a forward wave:
+//   wait for the producers of its k-steps of h_{t-1} (the next step's input
+//   projections are asked for first: left to the end of the product, the
+//   publish waited for them, 2-3 us a step at 128 rows), stream the k-steps
+//   from the exchange ring (device-scope loads, 8 k-steps of 2 KB in flight)
+//   against the weights in LDS, add the shares, run the cell, store h_t into
+//   the ring with device-scope stores (written through to where every XCD's
+//   loads see it), set the wave's exchange flag; then the h history, stack
+//   and y.
+// One step of a gradient wave:
+//   phase B': wait for the KG KW partial products of its column group, sum
+//     them for its share of the cells, run the cell, dz into the ring, flag;
+//   phase A': wait for the producers of its k-steps of dz_t, stream them
+//     against the weights (32x32 MFMAs), store the 32 x 64 partial product
+//     into the XCD's L2 and set the wave's partial flag.
 //
-// What is reused when.  Ring slot t % 2 is rewritten at step t + 2 by a wave
-// that has waited for every partial of its group at step t + 2 (t - 2): the
-// waves behind them have waited for the exchange flags of step t + 1 of, taken
-// together, every producer of the row group, each set after its wave read
-// slot t % 2.  There is one partial slot: a wave stores its partial of step
-// t only after every wave of its column group has set its exchange flag of
-// step t - 1 (gradient: of step t), which follows the reads of the previous
-// partial.  Every wait has the loop's wall-clock limit and abort flag.
+// What is reused when.  Ring slot t % 2 is rewritten at step t + 2 (t - 2) by
+// a cell wave whose shares have, taken together, waited for the exchange
+// flags of step t + 1 (t - 1) of every producer of the row group, each set
+// after all the shares of its work-group read slot t % 2.  Forward, a share's
+// LDS slot is rewritten once the cell wave's flag says that it has read it.
+// Gradient, there is one partial slot: a wave stores its partial of step t
+// only after every wave of its column group has set its exchange flag of step
+// t, which follows the reads of the previous partial.  Every wait has the
+// loop's wall-clock limit and abort flag.
 //
-// Exchange blocks are 1 KB, one k-step (16 bf16 or 8 f32 columns) of 32 rows
-// in the matrix cores' operand order: lane l holds row l % 32, 16-byte chunk
-// l / 32.  The reduction runs over units forward and over 4 unit + gate in the
-// gradient, so a unit's four dz values are adjacent.  W^T rows, the input
-// projection's columns and the stack's gate values are in the same
-// 4 unit + gate order: one 16-byte access per row and unit.
+// Exchange blocks are 1 KB.  Forward: 16 rows of one k-step (32 bf16 or 16
+// f32 columns), lane l's 16 bytes being row l % 16, chunk l / 16.  Gradient:
+// 32 rows of 16 bf16 or 8 f32 columns, row l % 32, chunk l / 32.  The
+// reduction runs over units forward and over 4 unit + gate in the gradient,
+// so a unit's four dz values are adjacent.  W^T rows, the input projection's
+// columns and the stack's gate values are in the same 4 unit + gate order:
+// one 16-byte access per row and unit.
 //
-// Bound at bf16 H = 2048, B = 256, per step and compute unit: 512 KB of
-// exchange blocks from the L2 (4.3 us at the measured 50 B/clk), 1 MB of LDS
-// weight reads (3.4 us at 128 B/clk) beside 33.5 MFLOP (3.4 us).
+// Bound at bf16 H = 2048, B = 256, per step and compute unit: forward 1 MB of
+// exchange blocks from the L2 (8.7 us at the measured 50 B/clk; the counters
+// show 15 % of these requests waiting for a line on its way from the other
+// XCDs), gradient 512 KB; 1 MB of LDS weight reads (3.4 us at 128 B/clk)
+// beside 33.5 MFLOP (3.4 us).  A step of few rows is bound by the exchange
+// itself: 7-8 us from one publish to the next at 32 rows.
 #include <type_traits>
 
 #include "ll_kernels.h"
@@ -90,7 +103,7 @@ __device__ __forceinline__ f32x16 mfma32<float>(uint4 a, uint4 b, f32x16 c) {
   return c;
 }
 
-// KG: reduction slices; KW: waves that share a slice.
+// The gradient's split.  KG: reduction slices; KW: waves that share a slice.
 template <typename T, int KG_, int KW_>
 struct CShape {
   static constexpr int KPC = Op<T>::kPerChunk;
@@ -156,9 +169,9 @@ __device__ __forceinline__ void st16_dev(__amdgpu_buffer_rsrc_t r, unsigned off,
 template <typename T>
 constexpr int c_unroll() { return sizeof(T) == 2 ? 8 : 4; }
 template <typename T>
-__host__ __device__ constexpr int c_share(int KS, int KW) {   // padded k-steps of a share of the slice
+__host__ __device__ constexpr int c_share(int KS, int KW, int U = c_unroll<T>()) {   // padded k-steps of a share of the slice
   const int n = (KS + KW - 1) / KW;
-  return (n + c_unroll<T>() - 1) / c_unroll<T>() * c_unroll<T>();
+  return (n + U - 1) / U * U;
 }
 
 // The wave's partial product: acc[ct] += ring blocks (rs, 1 KB each, zeros
@@ -251,89 +264,219 @@ __device__ __forceinline__ int group_len(const CLoopArgs& a, int rg, int T_eff) 
 }  // namespace
 
 // ---------------------------------------------------------------------------
-// Forward loop, chip-wide.
+// Forward loop, chip-wide.  Work-group wg owns KPC hidden units (8 bf16, 4
+// f32): the 16 NT gate columns of the whole reduction.  The weights are the
+// first matrix-core operand, rows 4 unit + gate, and the 32 batch rows of a
+// wave the columns, so a result register quad is the four gates of one
+// (row, unit): the cell runs where the product ends.  One product step for
+// lane 16 q + l: rows l of the two row tiles, units NT q .. NT q + NT - 1.
 // ---------------------------------------------------------------------------
-template <typename T, int KG, int KW>
+// k-steps (2 KB of ring blocks each) of a wave's loop body and in flight
+constexpr int kFwdUnroll = 8;
+template <typename T, int KW_>
+struct CFwd {
+  static constexpr int KPC = Op<T>::kPerChunk;
+  static constexpr int KW = KW_;
+  static constexpr int RW = CNW / KW;            // row groups
+  static constexpr int NT = KPC / 4;             // weight tiles: units per lane and row
+  static constexpr int RT = KW == 1 ? 2 : 1;     // row tiles of a cell wave
+  static constexpr int NCF = KW == 1 ? 1 : 2;    // cell waves (exchange flags) per row group
+};
+// LDS of the forward kernel: weights, the shares' partial products on their
+// way to the cell waves, the flags of that hand-over.
+template <typename T, int KW>
+__host__ __device__ constexpr int cfwd_weight_chunks(int KS) {
+  return KW * c_share<T>(KS, KW, kFwdUnroll) * CFwd<T, KW>::NT * 64;
+}
+template <typename T, int KW>
+__host__ __device__ constexpr int cfwd_part_chunks() {
+  return CFwd<T, KW>::RW * 2 * (KW - 1) * CFwd<T, KW>::NT * 64;
+}
+template <typename T, int KW>
+constexpr size_t cfwd_lds(int H) {
+  const int KS = H / (4 * Op<T>::kPerChunk);
+  return (size_t)(cfwd_weight_chunks<T, KW>(KS) + cfwd_part_chunks<T, KW>()) * 16 + (CNW + 2 * CNW) * 4;
+}
+
+// Wait until the n <= 256 flags of the range are all >= need (n % 4 == 0, 16
+// bytes per lane and poll).
+__device__ __forceinline__ void wait_quads(const CLoopArgs& a, __amdgpu_buffer_rsrc_t flags, int n, unsigned need) {
+  const int lane = threadIdx.x & 63;
+  const bool mine = lane * 4 < n;
+  unsigned long long t0 = 0;
+  unsigned polls = 0;
+  while (true) {
+    const uint4 f = ld_chunk_l2(flags, mine ? (unsigned)(lane * 16) : kOOB);
+    const bool late = mine && (f.x < need || f.y < need || f.z < need || f.w < need);
+    if (__builtin_amdgcn_ballot_w64(late) == 0) break;
+    if (polls == 0) t0 = wall_clock64();
+    __builtin_amdgcn_s_sleep(1);
+    asm volatile("" ::: "memory");   // (every poll loads again)
+    if ((++polls & 255u) == 0) {
+      if (__hip_atomic_load(a.abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
+      if (wall_clock64() - t0 > a.limit) {
+        __hip_atomic_fetch_or(a.err, LL_DEVERR_BARRIER_BIT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(a.abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        break;
+      }
+    }
+  }
+  asm volatile("" ::: "memory");
+}
+// The same for flags in LDS, one per lane with `mine` set.
+__device__ __forceinline__ void wait_lds(const CLoopArgs& a, const unsigned* flags, int idx, bool mine, unsigned need) {
+  unsigned long long t0 = 0;
+  unsigned polls = 0;
+  while (true) {
+    const unsigned f = __hip_atomic_load(flags + (mine ? idx : 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (__builtin_amdgcn_ballot_w64(mine && f < need) == 0) break;
+    if (polls == 0) t0 = wall_clock64();
+    __builtin_amdgcn_s_sleep(1);
+    if ((++polls & 255u) == 0) {
+      if (__hip_atomic_load(a.abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
+      if (wall_clock64() - t0 > a.limit) {
+        __hip_atomic_fetch_or(a.err, LL_DEVERR_BARRIER_BIT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(a.abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        break;
+      }
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+__device__ __forceinline__ void set_lds(unsigned* flag, unsigned value) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  if ((threadIdx.x & 63) == 0) __hip_atomic_store(flag, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// The wave's product: acc[nt][rt] += weight tile nt (LDS, NT KB per k-step)
+// times row tile rt of the ring blocks (rs, 2 KB per k-step, zeros past the
+// range), k-steps [0, U ng) in groups of U from group `rot` on, around (the
+// work-groups of an XCD read the same freshly written blocks and start
+// apart).  Even and odd k-steps sum apart (half the length of a rounding
+// chain).
+template <typename T, int NT>
+__device__ __forceinline__ void cfwd_product(__amdgpu_buffer_rsrc_t rs, const uint4* w, int ng, int rot,
+                                             f32x4 (&acc)[NT][2]) {
+  constexpr int U = kFwdUnroll;
+  const int lane = threadIdx.x & 63;
+  uint4 b[U][2], wv[2][2 * NT];
+  f32x4 s[2][NT][2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int n = 0; n < NT; ++n) s[k][n][0] = s[k][n][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const uint4* wl = w + lane;
+  auto rd = [&](uint4 (&v)[2 * NT], int g, int c) {   // weights of k-steps 2c, 2c + 1 of group g
+#pragma unroll
+    for (int i = 0; i < 2 * NT; ++i) v[i] = wl[((g * U + 2 * c) * NT + i) * 64];
+  };
+  int cur = rot % ng;
+#pragma unroll
+  for (int i = 0; i < U; ++i)
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt)
+      b[i][rt] = ld_chunk_l2(rs, (unsigned)(((cur * U + i) * 2 + rt) << 10) + lane * 16);
+  rd(wv[0], cur, 0);
+  for (int left = ng; left > 0; --left) {
+    const int nxt = cur + 1 < ng ? cur + 1 : 0;
+#pragma unroll
+    for (int c = 0; c < U / 2; ++c) {
+      rd(wv[(c + 1) & 1], c + 1 < U / 2 ? cur : nxt, c + 1 < U / 2 ? c + 1 : 0);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int i = 2 * c + k;
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+#pragma unroll
+          for (int rt = 0; rt < 2; ++rt) s[k][n][rt] = Mfma<T>::step(wv[c & 1][k * NT + n], b[i][rt], s[k][n][rt]);
+        // (the last group asks past the range: no traffic)
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt)
+          b[i][rt] = ld_chunk_l2(rs, left > 1 ? (unsigned)(((nxt * U + i) * 2 + rt) << 10) + lane * 16 : kOOB);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    cur = nxt;
+  }
+#pragma unroll
+  for (int n = 0; n < NT; ++n)
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) acc[n][rt] = s[0][n][rt] + s[1][n][rt];
+}
+
+template <typename T, int KW>
 __global__ __launch_bounds__(CNT, 1) void cfwd_kernel(CLoopArgs a) {
-  using S = CShape<T, KG, KW>;
-  constexpr int KPC = S::KPC, NGX = S::NGX, CW = S::CW, RW = S::RW, RPK = S::RPK, RPL = S::RPL, NP = S::NP;
+  using S = CFwd<T, KW>;
+  constexpr int KPC = S::KPC, RW = S::RW, NT = S::NT, RT = S::RT, NCF = S::NCF;
   extern __shared__ uint4 lds[];
-  __shared__ int s_info[2];
-  join_group(a.rank_ctr, s_info);
-  const int x = uni(s_info[0]), rank = uni(s_info[1]);
   const int H = a.H, B = a.B, RGN = a.RGN;
-  if (x >= 8 || rank >= 32 || RGN > RW || H > 8 * 16 * NGX) {
-    c_fail(a);
+  const int wg = blockIdx.x, jb = wg * KPC;
+  if (RGN > RW || H > 256 * KPC || jb >= H) {
+    if (jb < H) c_fail(a);
     return;
   }
-  const int gpx = (H / 16 + 7) / 8;              // column groups per XCD
-  const int kq = rank / NGX, nq = rank % NGX, grp = x * gpx + nq;
-  if (nq >= gpx || grp * 16 >= H) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
-  const int KS = H / 32, KSP = c_share<T>(KS, KW);   // k-steps of the slice; of a share, padded
+  const int q = lane >> 4, l16 = lane & 15;
+  const int KS = H / (4 * KPC), KSP = c_share<T>(KS, KW, kFwdUnroll);   // k-steps; of a share, padded
   const long G4 = 4L * H, H5 = 5L * H;
+  uint4* parts = lds + cfwd_weight_chunks<T, KW>(KS);
+  unsigned* pf = reinterpret_cast<unsigned*>(parts + cfwd_part_chunks<T, KW>());   // [wave]: partials stored
+  unsigned* rf = pf + CNW;                                                         // [row group][row tile]: read
+  if (tid < 3 * CNW) pf[tid] = 0u;
   {
-    // weights: local column c = gate * 16 + u of unit grp * 16 + u
-    const T* WT = reinterpret_cast<const T*>(a.W) + a.woff + (long)kq * KS * 2 * KPC;
-    for (int i = tid; i < KW * KSP * 128; i += CNT) {
-      const int l = i & 63, c = ((i >> 6) & 1) * 32 + (l & 31), sh = (i >> 7) / KSP;
-      const int ks = sh * KS / KW + (i >> 7) - sh * KSP;
+    // weights: row m of tile n is gate m % 4 of unit NT (m / 4) + n
+    const T* WT = reinterpret_cast<const T*>(a.W) + a.woff;
+    for (int i = tid; i < KW * KSP * NT * 64; i += CNT) {
+      const int l = i & 63, m = l & 15, n = (i >> 6) % NT, kk = (i >> 6) / NT, sh = kk / KSP;
+      const int ks = sh * KS / KW + kk - sh * KSP;
       lds[i] = ks < (sh + 1) * KS / KW
-                   ? ld16(WT + (4L * (grp * 16 + (c & 15)) + (c >> 4)) * a.ldw + (2 * ks + (l >> 5)) * KPC)
+                   ? ld16(WT + (4L * (jb + NT * (m >> 2) + n) + (m & 3)) * a.ldw + (4 * ks + (l >> 4)) * KPC)
                    : zero4();
     }
   }
   __syncthreads();
   const int rg = wave % RW, kw = wave / RW;
   if (rg >= RGN) return;
-  float* sc = reinterpret_cast<float*>(lds + KW * KSP * 128) + wave * (kScratch / 4);
-  float* sc_h = sc;                    // [RPK][CW] h_t
-  float* sc_c = sc + RPK * CW;         // [RPK][CW] c_t
-
-  // cells of this wave: unit uu of the work-group's CW, rows lr .. lr + RPL - 1
-  const int uu = lane % CW, lr = kw * RPK + (lane / CW) * RPL;
-  const bool cellt = lane / CW < RPK / RPL;
-  const int jb = grp * 16 + kq * CW, j = jb + uu;
-  // row-wise stores: 16 bytes of the units of one row (h), four floats (y, c)
-  const int hr = kw * RPK + lane;                          // lanes < RPK
-  const int yr = kw * RPK + lane / (CW / 4), yc = (lane % (CW / 4)) * 4;
-  const bool hst = lane < RPK, yst = lane < RPK * (CW / 4);
-  const int yb = yst && rg * 32 + yr < B ? a.perm[rg * 32 + yr] : -1;
-  int b[RPL];
-  float hs[RPL], cs[RPL];
+  // cells: row tiles rt0 .. rt0 + RT - 1, row l16 of each, units j .. j + NT - 1
+  const bool cellw = kw < NCF;
+  const int rt0 = cellw && KW > 1 ? kw : 0;
+  const int j = jb + NT * q;
+  int b[RT];
+  float hs[RT][NT], cs[RT][NT];
 #pragma unroll
-  for (int e = 0; e < RPL; ++e) {
-    const int r = rg * 32 + lr + e;
-    b[e] = cellt && r < B ? a.perm[r] : -1;
-    hs[e] = b[e] >= 0 && a.h0 ? a.h0[(long)b[e] * H + j] : 0.f;
-    cs[e] = b[e] >= 0 && a.c0 ? a.c0[(long)b[e] * H + j] : 0.f;
+  for (int e = 0; e < RT; ++e) {
+    const int r = rg * 32 + (rt0 + e) * 16 + l16;
+    b[e] = cellw && r < B ? a.perm[r] : -1;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      hs[e][n] = b[e] >= 0 && a.h0 ? a.h0[(long)b[e] * H + j + n] : 0.f;
+      cs[e][n] = b[e] >= 0 && a.c0 ? a.c0[(long)b[e] * H + j + n] : 0.f;
+    }
   }
 
   const int T_eff = uni(a.meta[0]);
   const int len = group_len(a, rg, T_eff);
-  // this wave's k-steps of the slice and their producers' flags
+  // this wave's k-steps (a k-step is the units of four work-groups) and their
+  // producers' flags
   const int ks0 = kw * KS / KW, nks = (kw + 1) * KS / KW - ks0;
-  const int ksg = kq * KS + ks0;                           // first k-step of the row group's H / (2 KPC)
-  const int KSR = KG * KS;
-  const unsigned* in_flags = a.xflags + ((long)rg * 256 + 2 * ksg) * KW;
-  const unsigned* grp_flags = a.xflags + ((long)rg * 256 + grp * KG) * KW;
-  unsigned* my_xflag = a.xflags + ((long)rg * 256 + grp * KG + kq) * KW + kw;
-  const long pbase = (((long)x * RGN + rg) * NGX + nq) * NP;
-  unsigned* my_pflag = a.pflags + pbase + kq * KW + kw;
-  float* my_part = a.part + (pbase + kq * KW + kw) * kPartFloats;
-  const __amdgpu_buffer_rsrc_t rpart = make_rsrc(a.part + pbase * kPartFloats, NP * kPartFloats * 4);
-  const __amdgpu_buffer_rsrc_t rring = make_rsrc(a.ring, (unsigned)(2 * RGN * KSR) << 10);
-  const uint4* w = lds + kw * KSP * 128;
-  // ring chunk of (row, the work-group's CW = KPC units)
-  const unsigned hoff = (unsigned)(((jb / (2 * KPC)) << 10) + (((jb / KPC) & 1) * 32 + hr) * 16);
+  const int nfl = 4 * nks * NCF;
+  const __amdgpu_buffer_rsrc_t rfl = make_rsrc(a.xflags + ((long)rg * 256 + 4 * ks0) * NCF, (unsigned)nfl * 4);
+  unsigned* my_xflag = a.xflags + ((long)rg * 256 + wg) * NCF + (cellw ? kw : 0);
+  const __amdgpu_buffer_rsrc_t rring = make_rsrc(a.ring, (unsigned)(2 * RGN * KS) << 11);
+  const uint4* w = lds + kw * KSP * NT * 64;
+  // ring dword of (row tile 0, row l16, the lane's units)
+  const unsigned hoff = (unsigned)(((wg >> 2) << 11) + ((wg & 3) * 16 + l16) * 16 + q * 4);
 
-  float4 zx[RPL];
+  float4 zx[RT][NT];
   auto load_zx = [&](int A, long off) {
     const int nr = max(0, min(32, A - rg * 32));
     const __amdgpu_buffer_rsrc_t rz = make_rsrc(a.Zx + (off + rg * 32) * G4, (unsigned)(nr * G4 * 4));
 #pragma unroll
-    for (int e = 0; e < RPL; ++e)
-      zx[e] = ld_f32x4(rz, cellt ? (unsigned)(((lr + e) * G4 + 4 * j) * 4) : kOOB);
+    for (int e = 0; e < RT; ++e)
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+        zx[e][n] = ld_f32x4(rz, cellw ? (unsigned)((((rt0 + e) * 16 + l16) * G4 + 4 * (j + n)) * 4) : kOOB);
   };
   int A_t = len > 0 ? uni(a.active[0]) : 0;
   long off_t = 0;
@@ -342,108 +485,120 @@ __global__ __launch_bounds__(CNT, 1) void cfwd_kernel(CLoopArgs a) {
   for (int t = 0; t < len; ++t) {
     const int A_n = uni(a.active[t + 1]);
     const int nr = min(32, A_t - rg * 32);                 // rows of the group running at t
-    // ---- phase A
-    if (t > 0) wait_range(a, in_flags, 2 * nks * KW, (unsigned)(t + 1));
-    f32x16 acc[2] = {f32x16{}, f32x16{}};
-    float4 zc[RPL];
-    c_product<T>(make_rsrc(reinterpret_cast<char*>(a.ring) + (((long)((t + 1) & 1) * RGN + rg) * KSR + ksg) * 1024,
-                           (unsigned)nks << 10),
-                 w, KSP / c_unroll<T>(), nq, acc, [&]() {
+    // the next step's input projections: asked for before the exchange wait,
+    // so that the publish below does not wait for them
+    float4 zc[RT][NT];
 #pragma unroll
-                   for (int e = 0; e < RPL; ++e) zc[e] = zx[e];
-                   load_zx(A_n, off_t + A_t);
-                 });
-    if (t > 0) wait_range(a, grp_flags, NP, (unsigned)(t + 1));
-    store_partial(my_part, acc);
-    wait_all_vm();
-    if (lane == 0) __hip_atomic_store(my_pflag, (unsigned)(t + 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    // ---- phase B
-    wait_range(a, a.pflags + pbase, NP, (unsigned)(t + 2));
-    float z[RPL][4];
-    {
-      float pv[NP][4][RPL];
+    for (int e = 0; e < RT; ++e)
 #pragma unroll
-      for (int p = 0; p < NP; ++p)
+      for (int n = 0; n < NT; ++n) zc[e][n] = zx[e][n];
+    load_zx(A_n, off_t + A_t);
+    if (t > 0 && nks > 0) wait_quads(a, rfl, nfl, (unsigned)(t + 1));
+    f32x4 acc[NT][2];
+    cfwd_product<T, NT>(make_rsrc(reinterpret_cast<char*>(a.ring) + (((long)((t + 1) & 1) * RGN + rg) * KS + ks0) * 2048,
+                                  (unsigned)nks << 11),
+                        w, KSP / kFwdUnroll, wg >> 3, acc);
+    if constexpr (KW > 1) {
+      // the shares meet in LDS: each stores its product of the row tiles that
+      // are not its own (once their cell waves have read step t-1's), wave
+      // kw < 2 adds those of row tile kw in share order
+      wait_lds(a, rf, rg * 2 + (lane & 1), lane < 2, (unsigned)t);
+      float4* p4 = reinterpret_cast<float4*>(parts);
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
-          load_partial<RPL>(rpart, p * kPartFloats * 4 + part_off(g * 16 + kq * CW + uu, lr & 31), pv[p][g]);
+      for (int rt = 0; rt < 2; ++rt)
+        if (kw != rt)
 #pragma unroll
-      for (int e = 0; e < RPL; ++e) {
-        z[e][0] = zc[e].x;
-        z[e][1] = zc[e].y;
-        z[e][2] = zc[e].z;
-        z[e][3] = zc[e].w;
-#pragma unroll
-        for (int p = 0; p < NP; ++p)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) z[e][g] += pv[p][g][e];
+          for (int n = 0; n < NT; ++n)
+            p4[(((rg * 2 + rt) * (KW - 1) + (kw < rt ? kw : kw - 1)) * NT + n) * 64 + lane] =
+                make_float4(acc[n][rt][0], acc[n][rt][1], acc[n][rt][2], acc[n][rt][3]);
+      set_lds(pf + wave, (unsigned)(t + 1));
+      if (!cellw) {
+        off_t += A_t;
+        A_t = A_n;
+        continue;
       }
+      wait_lds(a, pf, (lane % KW) * RW + rg, lane < KW, (unsigned)(t + 1));
+#pragma unroll
+      for (int n = 0; n < NT; ++n) {
+        f32x4 v = rt0 ? acc[n][1] : acc[n][0];
+#pragma unroll
+        for (int s = 0; s < KW - 1; ++s) {
+          const float4 u = p4[(((rg * 2 + rt0) * (KW - 1) + s) * NT + n) * 64 + lane];
+          v += f32x4{u.x, u.y, u.z, u.w};
+        }
+        acc[n][0] = v;
+      }
+      set_lds(rf + rg * 2 + kw, (unsigned)(t + 1));
     }
+    float4 gv[RT][NT];
+    unsigned hv[RT];
 #pragma unroll
-    for (int e = 0; e < RPL; ++e) {
-      z[e][0] = sigmoidf_(z[e][0]);
-      z[e][1] = sigmoidf_(z[e][1]);
-      z[e][2] = tanhf_(z[e][2]);
-      z[e][3] = sigmoidf_(z[e][3]);
-      const float cn = z[e][1] * cs[e] + z[e][0] * z[e][2];
-      const float hn = z[e][3] * tanhf_(cn);
-      if (lr + e < nr) {
-        cs[e] = cn;
-        hs[e] = hn;
+    for (int e = 0; e < RT; ++e) {
+      const int r = (rt0 + e) * 16 + l16;
+#pragma unroll
+      for (int n = 0; n < NT; ++n) {
+        const float ig = sigmoidf_(acc[n][e][0] + zc[e][n].x), fg = sigmoidf_(acc[n][e][1] + zc[e][n].y);
+        const float gg = tanhf_(acc[n][e][2] + zc[e][n].z), og = sigmoidf_(acc[n][e][3] + zc[e][n].w);
+        const float cn = lstm_c(ig, fg, gg, cs[e][n]);
+        const float hn = og * tanhf_(cn);
+        if (r < nr) {
+          cs[e][n] = cn;
+          hs[e][n] = hn;
+        }
+        gv[e][n] = make_float4(ig, fg, gg, og);
       }
-      if (cellt) {
-        sc_h[(lr - kw * RPK + e) * CW + uu] = hs[e];
-        sc_c[(lr - kw * RPK + e) * CW + uu] = cs[e];
-      }
-    }
-    wave_lds_fence();
-    uint4 hv = zero4();
-    if (hst) {
-      const float4* s4 = reinterpret_cast<const float4*>(sc_h + lane * CW);
-      if constexpr (sizeof(T) == 4) {
-        hv = __builtin_bit_cast(uint4, s4[0]);
-      } else {
-        const float4 u = s4[0], v = s4[1];
-        hv.x = (unsigned)f32_to_bf16(u.x) | ((unsigned)f32_to_bf16(u.y) << 16);
-        hv.y = (unsigned)f32_to_bf16(u.z) | ((unsigned)f32_to_bf16(u.w) << 16);
-        hv.z = (unsigned)f32_to_bf16(v.x) | ((unsigned)f32_to_bf16(v.y) << 16);
-        hv.w = (unsigned)f32_to_bf16(v.z) | ((unsigned)f32_to_bf16(v.w) << 16);
-      }
-      if (hr < nr) st16_dev(rring, (unsigned)(((t & 1) * RGN + rg) * KSR) * 1024u + hoff, hv);
+      if constexpr (NT == 1)
+        hv[e] = __float_as_uint(hs[e][0]);
+      else
+        hv[e] = (unsigned)f32_to_bf16(hs[e][0]) | ((unsigned)f32_to_bf16(hs[e][NT - 1]) << 16);
+      if (r < nr)
+        st_dev(rring, (unsigned)((((t & 1) * RGN + rg) * KS) << 11) + ((unsigned)(rt0 + e) << 10) + hoff,
+               __uint_as_float(hv[e]));
     }
     wait_all_vm();
     if (lane == 0) __hip_atomic_store(my_xflag, (unsigned)(t + 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // h history, stack row and y of step t
-    const long cr0 = off_t + rg * 32;
-    if (hst && hr < nr) *reinterpret_cast<uint4*>(reinterpret_cast<T*>(a.X) + (cr0 + hr) * H + jb) = hv;
-    if (a.stack) {
 #pragma unroll
-      for (int e = 0; e < RPL; ++e)
-        if (cellt && lr + e < nr)
-          *reinterpret_cast<float4*>(a.stack + (cr0 + lr + e) * H5 + 4 * j) =
-              make_float4(z[e][0], z[e][1], z[e][2], z[e][3]);
-      if (yst && yr < nr)
-        *reinterpret_cast<float4*>(a.stack + (cr0 + yr) * H5 + G4 + jb + yc) =
-            *reinterpret_cast<const float4*>(sc_c + (yr - kw * RPK) * CW + yc);
+    for (int e = 0; e < RT; ++e) {
+      const int r = (rt0 + e) * 16 + l16;
+      const long cr = off_t + rg * 32 + r;
+      if (r < nr) {
+        *reinterpret_cast<unsigned*>(reinterpret_cast<T*>(a.X) + cr * H + j) = hv[e];
+        if (a.stack) {
+          float* srow = a.stack + cr * H5;
+#pragma unroll
+          for (int n = 0; n < NT; ++n) *reinterpret_cast<float4*>(srow + 4 * (j + n)) = gv[e][n];
+          if constexpr (NT == 1)
+            srow[G4 + j] = cs[e][0];
+          else
+            *reinterpret_cast<float2*>(srow + G4 + j) = make_float2(cs[e][0], cs[e][NT - 1]);
+        }
+      }
+      if (a.y && b[e] >= 0) {
+        float* yp = a.y + ((long)t * B + b[e]) * H + j;
+        if constexpr (NT == 1)
+          yp[0] = r < nr ? hs[e][0] : 0.f;
+        else
+          *reinterpret_cast<float2*>(yp) = r < nr ? make_float2(hs[e][0], hs[e][NT - 1]) : make_float2(0.f, 0.f);
+      }
     }
-    if (a.y && yb >= 0)
-      *reinterpret_cast<float4*>(a.y + ((long)t * B + yb) * H + jb + yc) =
-          yr < nr ? *reinterpret_cast<const float4*>(sc_h + (yr - kw * RPK) * CW + yc) : make_float4(0.f, 0.f, 0.f, 0.f);
-    wave_lds_fence();
     off_t += A_t;
     A_t = A_n;
   }
 
 #pragma unroll
-  for (int e = 0; e < RPL; ++e) {
+  for (int e = 0; e < RT; ++e) {
     if (b[e] < 0) continue;
-    a.hT[(long)b[e] * H + j] = hs[e];
-    a.cT[(long)b[e] * H + j] = cs[e];
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      a.hT[(long)b[e] * H + j + n] = hs[e][n];
+      a.cT[(long)b[e] * H + j + n] = cs[e][n];
+    }
   }
-  // y past the group's last step: whole rows, the steps dealt to the column
-  // groups' work-groups, the rows to the waves of the slice
+  // y past the group's last step: whole rows, the steps dealt to the
+  // work-groups, the rows to the waves of the row group
   if (a.y) {
-    const int nwg = (H / 16) * KG, wg = grp * KG + kq;
+    const int nwg = H / KPC;
     const int rows = min(32, B - rg * 32);
     for (int t = len + wg; t < a.T_max; t += nwg)
       for (int r = kw; r < rows; r += KW) {
@@ -749,23 +904,24 @@ __global__ __launch_bounds__(CNT, 1) void cbwd_kernel(CLoopArgs a) {
 }
 
 // Set-up: h0 rows into ring slot 1 in the consumers' order, flags to zero.
-//   f = ((m * KS + ks) * 64 + l) * KPC + e: row m*32 + l % 32,
-//   unit (2 ks + l / 32) * KPC + e.
+//   f = (((m * KS + ks) * 2 + rt) * 64 + l) * KPC + e: row m*32 + rt*16 + l % 16,
+//   unit (4 ks + l / 16) * KPC + e.
 template <typename T>
 __global__ __launch_bounds__(256) void c_prepare_kernel(const float* __restrict__ h0,
                                                         const int* __restrict__ perm, int B, int H, int RGN,
                                                         void* ring, unsigned* flags, int nflags) {
   constexpr int KPC = Op<T>::kPerChunk;
-  const int KS = H / (2 * KPC);
-  const long n = (long)RGN * KS * 64 * KPC;
+  const int KS = H / (4 * KPC);
+  const long n = (long)RGN * KS * 128 * KPC;
   T* slot1 = reinterpret_cast<T*>(ring) + n;
   for (long f = blockIdx.x * 256L + threadIdx.x; f < n; f += gridDim.x * 256L) {
     const int e = (int)(f % KPC);
     const int l = (int)((f / KPC) % 64);
-    const int ks = (int)((f / (64 * KPC)) % KS);
-    const int m = (int)(f / (64L * KPC * KS));
-    const int r = m * 32 + (l & 31);
-    const int u = (2 * ks + (l >> 5)) * KPC + e;
+    const int rt = (int)((f / (64 * KPC)) & 1);
+    const int ks = (int)((f / (128 * KPC)) % KS);
+    const int m = (int)(f / (128L * KPC * KS));
+    const int r = m * 32 + rt * 16 + (l & 15);
+    const int u = (4 * ks + (l >> 4)) * KPC + e;
     slot1[f] = Op<T>::from_f32((h0 && r < B) ? h0[(long)perm[r] * H + u] : 0.f);
   }
   for (long i = blockIdx.x * 256L + threadIdx.x; i < nflags; i += gridDim.x * 256L) flags[i] = 0u;
@@ -788,16 +944,19 @@ template hipError_t launch_c_prepare<bf16_t>(const float*, const int*, int, int,
                                              hipStream_t);
 
 namespace {
-template <typename T, int KW>
+// KW, KWF: shares of the gradient's slices and of the forward's reduction
+template <typename T, int KW, int KWF>
 CKernels c_make(int H, int rgn) {
-  constexpr int KGF = sizeof(T) == 2 ? 2 : 4, KGB = 4 * KGF;
+  constexpr int KGB = sizeof(T) == 2 ? 8 : 16;
   CKernels k{};
-  k.fwd = reinterpret_cast<const void*>(&cfwd_kernel<T, KGF, KW>);
+  k.fwd = reinterpret_cast<const void*>(&cfwd_kernel<T, KWF>);
   k.bwd = reinterpret_cast<const void*>(&cbwd_kernel<T, KGB, KW>);
-  k.lds = (size_t)KW * c_share<T>(H / 32, KW) * 2048 + CNW * kScratch;
+  k.lds_fwd = cfwd_lds<T, KWF>(H);
+  k.lds_bwd = (size_t)KW * c_share<T>(H / 32, KW) * 2048 + CNW * kScratch;
   k.rgn = rgn;
   k.kw = KW;
-  k.cw = 16 / KGF;
+  k.cw = Op<T>::kPerChunk;
+  k.nwg_fwd = H / k.cw;
   k.part_floats = 8L * rgn * 32 * KW * kPartFloats;
   k.flag_words = 8 + rgn * 256 * KW + 8 * rgn * 32 * KW;
   return k;
@@ -810,7 +969,10 @@ template <typename T>
 CKernels c_kernels(int H, int B) {
   const int rgn = (B + 31) / 32;
   if (H % 32 || H < 64 || H > (sizeof(T) == 2 ? 2048 : 1024) || rgn < 1 || rgn > 8) return CKernels{};
-  return rgn <= 2 ? c_make<T, 4>(H, rgn) : rgn <= 4 ? c_make<T, 2>(H, rgn) : c_make<T, 1>(H, rgn);
+  return rgn <= 1   ? c_make<T, 4, 8>(H, rgn)
+         : rgn <= 2 ? c_make<T, 4, 4>(H, rgn)
+         : rgn <= 4 ? c_make<T, 2, 2>(H, rgn)
+                    : c_make<T, 1, 1>(H, rgn);
 }
 template CKernels c_kernels<float>(int, int);
 template CKernels c_kernels<bf16_t>(int, int);
@@ -826,19 +988,19 @@ hipError_t c_setup(const CKernels& k, int* occ_fwd, int* occ_bwd) {
     *occ_bwd = 0;
     return hipSuccess;
   }
-  e = hipFuncSetAttribute(k.fwd, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.lds);
+  e = hipFuncSetAttribute(k.fwd, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.lds_fwd);
   if (e != hipSuccess) return e;
-  e = hipFuncSetAttribute(k.bwd, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.lds);
+  e = hipFuncSetAttribute(k.bwd, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.lds_bwd);
   if (e != hipSuccess) return e;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(occ_fwd, k.fwd, CNT, k.lds);
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(occ_fwd, k.fwd, CNT, k.lds_fwd);
   if (e != hipSuccess) return e;
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(occ_bwd, k.bwd, CNT, k.lds);
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(occ_bwd, k.bwd, CNT, k.lds_bwd);
 }
 
-hipError_t c_launch(const void* fn, const CLoopArgs& a, size_t lds, hipStream_t s) {
+hipError_t c_launch(const void* fn, const CLoopArgs& a, int nwg, size_t lds, hipStream_t s) {
   CLoopArgs copy = a;
   void* kargs[] = {&copy};
-  return hipLaunchKernel(fn, dim3(256), dim3(CNT), kargs, lds, s);
+  return hipLaunchKernel(fn, dim3((unsigned)nwg), dim3(CNT), kargs, lds, s);
 }
 
 }  // namespace ll

@@ -348,12 +348,12 @@ struct CLoopArgs {
   int ldw;
   int woff;               // forward: column of the h part in W^T; backward: row of W_h
   void* X;                // forward: h history [cap, H]; backward: dz [cap, 4H] (operand type)
-  void* ring;             // exchange ring [2][RGN][H / (2 KPC) forward, 4H / (2 KPC) backward][1 KB]
-                          // (forward: slot 1 holds h0)
-  float* part;            // partial products [8][RGN][32][KW][32 x 64]
-  unsigned* xflags;       // exchange flags [RGN][256][KW] (one per cell block, row group and share)
-  unsigned* pflags;       // partial-product flags [8][RGN][32][KW]
-  unsigned* rank_ctr;     // [8]
+  void* ring;             // exchange ring [2][RGN][H / (4 KPC)][2][1 KB] forward (slot 1 holds h0),
+                          // [2][RGN][4H / (2 KPC)][1 KB] backward
+  float* part;            // backward: partial products [8][RGN][32][KW][32 x 64]
+  unsigned* xflags;       // exchange flags [RGN][256][cell waves of a row group: 1 or 2 forward, KW backward]
+  unsigned* pflags;       // backward: partial-product flags [8][RGN][32][KW]
+  unsigned* rank_ctr;     // backward: [8]
   const float* Zx;        // forward: [cap, 4H], column 4 u + g
   const float* h0;
   const float* c0;
@@ -377,9 +377,11 @@ struct CLoopArgs {
 struct CKernels {
   const void* fwd;
   const void* bwd;
-  size_t lds;
+  size_t lds_fwd;
+  size_t lds_bwd;
+  int nwg_fwd;            // work-groups of the forward loop
   int rgn;                // row groups of 32
-  int kw;                 // waves that share a reduction slice
+  int kw;                 // gradient: waves that share a reduction slice
   int cw;                 // cell units per work-group
   long part_floats;       // partial products
   int flag_words;         // [8] rank counters, exchange flags [rgn][256][kw], partial flags [8][rgn][32][kw]
@@ -387,7 +389,7 @@ struct CKernels {
 template <typename T>
 CKernels c_kernels(int H, int B);
 hipError_t c_setup(const CKernels& k, int* occ_fwd, int* occ_bwd);
-hipError_t c_launch(const void* fn, const CLoopArgs& a, size_t lds, hipStream_t s);
+hipError_t c_launch(const void* fn, const CLoopArgs& a, int nwg, size_t lds, hipStream_t s);
 // h0 rows (length order, operand type) into ring slot 1 and every flag and
 // rank counter of the launch to zero.
 template <typename T>

@@ -578,7 +578,7 @@ ll_status plan_configure(ll_plan* p, const ll_desc* desc, int device, const hipD
   // H <= 2048, f32 H <= 1024, B <= 256).
   if (!p->xmode && allow && p->n_cu == 256) {
     ll::CKernels ck = p->bf16 ? ll::c_kernels<bf16_t>(H, B) : ll::c_kernels<float>(H, B);
-    if (ck.fwd && ck.bwd && ck.lds + 64 <= lds_limit) {
+    if (ck.fwd && ck.bwd && std::max(ck.lds_fwd, ck.lds_bwd) + 64 <= lds_limit) {
       int of = 0, ob = 0;
       if (ll::c_setup(ck, &of, &ob) == hipSuccess && of >= 1 && ob >= 1) {
         p->cmode = true;
@@ -1376,7 +1376,7 @@ ll_status enqueue_fwd(ll_plan* p, hipStream_t s, const void* x, const int32_t* s
       ca.hT = hT + (long)l * B * H;
       ca.cT = cT + (long)l * B * H;
       ev = tbeg(p, s, LL_STAGE_FWD_LOOP);
-      LL_HIP(chained_loop_launch(p->device, s, [&] { return ll::c_launch(p->ck.fwd, ca, p->ck.lds, s); }));
+      LL_HIP(chained_loop_launch(p->device, s, [&] { return ll::c_launch(p->ck.fwd, ca, p->ck.nwg_fwd, p->ck.lds_fwd, s); }));
       tend(p, s, LL_STAGE_FWD_LOOP, ev);
       continue;
     }
@@ -2089,7 +2089,7 @@ ll_status enqueue_bwd(ll_plan* p, hipStream_t s, const float* dy, const float* d
       ca.dh0 = dh0 ? dh0 + (long)l * B * H : nullptr;
       ca.dc0 = dc0 ? dc0 + (long)l * B * H : nullptr;
       ev = tbeg(p, s, LL_STAGE_BWD_LOOP);
-      LL_HIP(chained_loop_launch(p->device, s, [&] { return ll::c_launch(p->ck.bwd, ca, p->ck.lds, s); }));
+      LL_HIP(chained_loop_launch(p->device, s, [&] { return ll::c_launch(p->ck.bwd, ca, 256, p->ck.lds_bwd, s); }));
       tend(p, s, LL_STAGE_BWD_LOOP, ev);
     }
     ll::BwdLoopArgs a{};

@@ -21,7 +21,10 @@ CASES = [W(f"chipw_{dtype}_b{B}_i{I}_h{H}_t{T}_l{L}", B=B, I=I, H=H, T_max=T, dt
              ("bf16", 1, 8, 1056, 6, 1), ("bf16", 33, 24, 1184, 5, 1), ("bf16", 64, 16, 1536, 5, 1),
              ("bf16", 65, 40, 1056, 5, 1), ("bf16", 128, 16, 2016, 4, 1), ("bf16", 129, 16, 1088, 5, 1),
              ("bf16", 256, 8, 1280, 4, 2), ("f32", 1, 4, 544, 6, 1), ("f32", 40, 20, 672, 6, 1),
-             ("f32", 66, 12, 992, 4, 1), ("f32", 130, 8, 544, 5, 2), ("f32", 256, 8, 608, 4, 1)], start=301)]
+             ("f32", 66, 12, 992, 4, 1), ("f32", 130, 8, 544, 5, 2), ("f32", 256, 8, 608, 4, 1),
+             # eight and four shares of the forward's reduction at the full LDS, and their last batch
+             ("bf16", 32, 8, 2048, 4, 1), ("bf16", 48, 8, 2048, 4, 1), ("f32", 32, 8, 1024, 4, 1),
+             ("f32", 17, 8, 576, 5, 1)], start=301)]
 
 
 @pytest.mark.parametrize("w", CASES, ids=[w.name for w in CASES])
