@@ -24,7 +24,7 @@
 // KG = 2 / 4 work-groups and their partial products in the L2 took, per step,
 // bf16 H = 2048 18.0 us (B = 64), 23.9 (128), 32.1 (256), H = 1536 15.7 (64),
 // 19.1 (128), f32 H = 640 16.4 (64), 15.2 (128); with the whole reduction per
-// work-group 11.7, 14.3, 31.3, 10.0, 11.3, 11.2, 11.8.  Above 128 rows the
+// work-group 11.7, 14.3, 31.3, 10.0, 11.3, 10.4, 11.8.  Above 128 rows the
 // 1 MB that every work-group then streams evens the two out (B = 160 to 192
 // of bf16 H = 2048 and 256 of f32 H = 1024 are 4-7 % slower than split, the
 // narrower widths 4-16 % faster).
@@ -271,8 +271,13 @@ __device__ __forceinline__ int group_len(const CLoopArgs& a, int rg, int T_eff) 
 // (row, unit): the cell runs where the product ends.  One product step for
 // lane 16 q + l: rows l of the two row tiles, units NT q .. NT q + NT - 1.
 // ---------------------------------------------------------------------------
-// k-steps (2 KB of ring blocks each) of a wave's loop body and in flight
-constexpr int kFwdUnroll = 8;
+// k-steps (2 KB of ring blocks each) of a wave's loop body and in flight.  A
+// share is padded to whole bodies: float32's short shares (KW >= 4) take 4,
+// for there the products of the padding cost more than the loads in flight
+// give (H = 640, B = 64 11.2 us a step with 8, 10.4 with 4; H = 1024 equal;
+// the longer shares of B = 128, H = 1024 17.3 with 8, 19.9 with 4).
+template <typename T, int KW>
+constexpr int cfwd_unroll() { return sizeof(T) == 4 && KW >= 4 ? 4 : 8; }
 template <typename T, int KW_>
 struct CFwd {
   static constexpr int KPC = Op<T>::kPerChunk;
@@ -286,7 +291,7 @@ struct CFwd {
 // way to the cell waves, the flags of that hand-over.
 template <typename T, int KW>
 __host__ __device__ constexpr int cfwd_weight_chunks(int KS) {
-  return KW * c_share<T>(KS, KW, kFwdUnroll) * CFwd<T, KW>::NT * 64;
+  return KW * c_share<T>(KS, KW, cfwd_unroll<T, KW>()) * CFwd<T, KW>::NT * 64;
 }
 template <typename T, int KW>
 __host__ __device__ constexpr int cfwd_part_chunks() {
@@ -354,10 +359,9 @@ __device__ __forceinline__ void set_lds(unsigned* flag, unsigned value) {
 // work-groups of an XCD read the same freshly written blocks and start
 // apart).  Even and odd k-steps sum apart (half the length of a rounding
 // chain).
-template <typename T, int NT>
+template <typename T, int NT, int U>
 __device__ __forceinline__ void cfwd_product(__amdgpu_buffer_rsrc_t rs, const uint4* w, int ng, int rot,
                                              f32x4 (&acc)[NT][2]) {
-  constexpr int U = kFwdUnroll;
   const int lane = threadIdx.x & 63;
   uint4 b[U][2], wv[2][2 * NT];
   f32x4 s[2][NT][2];
@@ -418,7 +422,7 @@ __global__ __launch_bounds__(CNT, 1) void cfwd_kernel(CLoopArgs a) {
   }
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
   const int q = lane >> 4, l16 = lane & 15;
-  const int KS = H / (4 * KPC), KSP = c_share<T>(KS, KW, kFwdUnroll);   // k-steps; of a share, padded
+  const int KS = H / (4 * KPC), KSP = c_share<T>(KS, KW, cfwd_unroll<T, KW>());   // k-steps; of a share, padded
   const long G4 = 4L * H, H5 = 5L * H;
   uint4* parts = lds + cfwd_weight_chunks<T, KW>(KS);
   unsigned* pf = reinterpret_cast<unsigned*>(parts + cfwd_part_chunks<T, KW>());   // [wave]: partials stored
@@ -495,9 +499,9 @@ __global__ __launch_bounds__(CNT, 1) void cfwd_kernel(CLoopArgs a) {
     load_zx(A_n, off_t + A_t);
     if (t > 0 && nks > 0) wait_quads(a, rfl, nfl, (unsigned)(t + 1));
     f32x4 acc[NT][2];
-    cfwd_product<T, NT>(make_rsrc(reinterpret_cast<char*>(a.ring) + (((long)((t + 1) & 1) * RGN + rg) * KS + ks0) * 2048,
+    cfwd_product<T, NT, cfwd_unroll<T, KW>()>(make_rsrc(reinterpret_cast<char*>(a.ring) + (((long)((t + 1) & 1) * RGN + rg) * KS + ks0) * 2048,
                                   (unsigned)nks << 11),
-                        w, KSP / kFwdUnroll, wg >> 3, acc);
+                        w, KSP / cfwd_unroll<T, KW>(), wg >> 3, acc);
     if constexpr (KW > 1) {
       // the shares meet in LDS: each stores its product of the row tiles that
       // are not its own (once their cell waves have read step t-1's), wave
