@@ -170,10 +170,13 @@ __global__ __launch_bounds__(kThreads) void gemm32_nt_kernel(GemmArgs g, unsigne
 // (k-slot l / 32) lie in different banks.  A load instruction fills 4 rows.
 // The row map of a k-tile is read a k-tile ahead of its fill.
 //
-// The sums of kSpan k-tiles (2048 rows) are gathered in a second set of
-// registers: a single float32 chain over 100 000 rows loses a digit.
+// The sums of kSpan k-tiles (256 rows) are gathered in a second set of
+// registers: the rounding error of one float32 chain grows with the square
+// root of its length (2-norm error of dW at 6400 rows of H = 256: 7.5e-7 with
+// spans of 2048 rows, 5.6e-7 with these).  No split of the reduction is
+// shorter than 256 rows, so no chain is longer than a split-K sum's.
 // ---------------------------------------------------------------------------
-constexpr int kSpan = 64;
+constexpr int kSpan = 8;   // (even: a span starts on the first stage)
 
 template <int S>
 __global__ __launch_bounds__(kThreads) void gemm32_tn_kernel(GemmTnArgs g, unsigned a_bytes, unsigned b_bytes,
