@@ -15,9 +15,8 @@
 //
 // Inside a work-group every wave runs the recurrence of its own rows alone:
 // the batch is cut into groups of 32 rows, wave w takes row group w % RW and
-// share w / RW of the work-group's reduction (RW KW = 8: KW = 1 for more than
-// 128 rows, 2 for more than 64, 4 below, and 8 forward for at most 32, so
-// that a small batch still spreads over the waves).  No barrier stands in a
+// share w / RW of the work-group's reduction (RW KW = 8; c_kernels says how
+// many and why).  No barrier stands in a
 // step: the shares meet in LDS behind flags (forward) or as partial products
 // of the group, like the KG slices (gradient), and the waves of a SIMD hide
 // each other's waits.  Measured: the forward loop with a reduction split over
@@ -962,20 +961,30 @@ CKernels c_make(int H, int rgn) {
   k.cw = Op<T>::kPerChunk;
   k.nwg_fwd = H / k.cw;
   k.part_floats = 8L * rgn * 32 * KW * kPartFloats;
-  k.flag_words = 8 + rgn * 256 * KW + 8 * rgn * 32 * KW;
+  k.flag_words = 8 + std::max(rgn * 256 * CFwd<T, KWF>::NCF, rgn * 256 * KW + 8 * rgn * 32 * KW);
   return k;
 }
 }  // namespace
 
 // Kernels for a (dtype, H, B): H % 32 == 0, one work-group per compute unit
 // for H = 2048 (bf16) / 1024 (f32), fewer below; at most 256 rows.
+//
+// Waves that share a slice of the gradient's reduction, us per step (rows: loop
+// with KW = 1, 2, 4, 8): a share more is a partial product more for every cell
+// to sum, so one wave per slice, bf16 H = 2048 16 rows: 7.5, 8.4, 7.7, 12.7;
+// 40: 10.3, 12.5, 14.5; 96: 13.2, 15.5; f32 H = 640 16: 9.3, 10.9, 10.8; 64:
+// 10.8, 13.1, 17.4; 96: 11.5, 17.5; only float32's long slices of one row
+// group are faster shared by four (H = 1024 16 rows: 13.0, 13.2, 11.5;
+// H = 768: 10.4, -, 10.5).
 template <typename T>
 CKernels c_kernels(int H, int B) {
   const int rgn = (B + 31) / 32;
   if (H % 32 || H < 64 || H > (sizeof(T) == 2 ? 2048 : 1024) || rgn < 1 || rgn > 8) return CKernels{};
-  return rgn <= 1   ? c_make<T, 4, 8>(H, rgn)
-         : rgn <= 2 ? c_make<T, 4, 4>(H, rgn)
-         : rgn <= 4 ? c_make<T, 2, 2>(H, rgn)
+  if constexpr (sizeof(T) == 4)
+    if (rgn <= 1 && H > 768) return c_make<T, 4, 8>(H, rgn);
+  return rgn <= 1   ? c_make<T, 1, 8>(H, rgn)
+         : rgn <= 2 ? c_make<T, 1, 4>(H, rgn)
+         : rgn <= 4 ? c_make<T, 1, 2>(H, rgn)
                     : c_make<T, 1, 1>(H, rgn);
 }
 template CKernels c_kernels<float>(int, int);

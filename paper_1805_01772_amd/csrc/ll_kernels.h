@@ -384,7 +384,8 @@ struct CKernels {
   int kw;                 // gradient: waves that share a reduction slice
   int cw;                 // cell units per work-group
   long part_floats;       // partial products
-  int flag_words;         // [8] rank counters, exchange flags [rgn][256][kw], partial flags [8][rgn][32][kw]
+  int flag_words;         // [8] rank counters; the gradient: exchange flags [rgn][256][kw], partial flags
+                          // [8][rgn][32][kw]; the forward: exchange flags [rgn][256][cell waves]
 };
 template <typename T>
 CKernels c_kernels(int H, int B);

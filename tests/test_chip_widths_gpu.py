@@ -25,6 +25,10 @@ CASES = [W(f"chipw_{dtype}_b{B}_i{I}_h{H}_t{T}_l{L}", B=B, I=I, H=H, T_max=T, dt
              # eight and four shares of the forward's reduction at the full LDS, and their last batch
              ("bf16", 32, 8, 2048, 4, 1), ("bf16", 48, 8, 2048, 4, 1), ("f32", 32, 8, 1024, 4, 1),
              ("f32", 17, 8, 576, 5, 1)], start=301)]
+# float32: the gradient's slices shared by four and by none either side of H = 768
+CASES += [W(f"chipw_f32_b{B}_i8_h{H}_t{T}", B=B, I=8, H=H, T_max=T, dtype="f32", len_lo=0, len_hi=T,
+            random_state=True, seed=seed)
+          for seed, (B, H, T) in enumerate([(30, 768, 4), (5, 800, 5), (64, 1024, 4), (97, 896, 4)], start=361)]
 
 
 @pytest.mark.parametrize("w", CASES, ids=[w.name for w in CASES])
