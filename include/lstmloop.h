@@ -308,7 +308,10 @@ ll_status lstm_loop_bwd(ll_plan* plan, void* stream,
  * device memory or create streams (code under HIP graph capture, tight
  * serving loops, harnesses that forbid allocation): computes exactly what
  * lstm_loop_fwd(plan for *desc, ..., save_for_backward = 0) computes, with the
- * same kernels, but without a plan.  Every buffer the forward needs (length
+ * same kernels, but without a plan.  (Where the buffers fit the scratch array
+ * but the exchange arrays of the chip-wide loops, or of the XCD-local loops at
+ * a bfloat16 width that is an odd multiple of 32, do not beside them, the
+ * grid-barrier loops run, as with LSTMLOOP_LOOPS=grid.)  Every buffer the forward needs (length
  * order, transposed weights, input projections, h history, exchange rings and
  * flags) is carved from a scratch array of LL_NOALLOC_SCRATCH_BYTES bytes that
  * the library holds in each device's memory from the moment it is loaded

@@ -961,7 +961,8 @@ CKernels c_make(int H, int rgn) {
   k.cw = Op<T>::kPerChunk;
   k.nwg_fwd = H / k.cw;
   k.part_floats = 8L * rgn * 32 * KW * kPartFloats;
-  k.flag_words = 8 + std::max(rgn * 256 * CFwd<T, KWF>::NCF, rgn * 256 * KW + 8 * rgn * 32 * KW);
+  k.flag_words_fwd = 8 + rgn * 256 * CFwd<T, KWF>::NCF;
+  k.flag_words = std::max(k.flag_words_fwd, 8 + rgn * 256 * KW + 8 * rgn * 32 * KW);
   return k;
 }
 }  // namespace

@@ -386,6 +386,7 @@ struct CKernels {
   long part_floats;       // partial products
   int flag_words;         // [8] rank counters; the gradient: exchange flags [rgn][256][kw], partial flags
                           // [8][rgn][32][kw]; the forward: exchange flags [rgn][256][cell waves]
+  int flag_words_fwd;     // the forward's alone
 };
 template <typename T>
 CKernels c_kernels(int H, int B);

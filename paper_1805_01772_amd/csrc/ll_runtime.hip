@@ -780,9 +780,13 @@ ll_status plan_layout(ll_plan* p, bool fwd_only, Take&& take) {
     }
   }
   if (p->cmode) {
-    // two slots x row groups x (H or 4H columns / k-step) blocks of 1 KB; partial products
+    // two slots x row groups x (H or 4H columns / k-step) blocks of 1 KB; the
+    // gradient's partial products (the forward loop has none)
     ALLOC(p->cring, 2L * p->ck.rgn * ((fwd_only ? 1L : 4L) * H * (long)es / 32) * 1024, "exchange ring");
-    ALLOC(p->cpart, sizeof(float) * p->ck.part_floats, "partial products");
+    if (fwd_only)
+      p->ck.flag_words = p->ck.flag_words_fwd;
+    else
+      ALLOC(p->cpart, sizeof(float) * p->ck.part_floats, "partial products");
     ALLOC(p->cflags, sizeof(unsigned) * p->ck.flag_words, "exchange flags");
   }
   if (p->skip) ALLOC(p->sx, sizeof(float) * cap, "predicate input part");

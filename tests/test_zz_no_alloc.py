@@ -94,3 +94,47 @@ def test_noalloc_limits_and_device_error():
     dc.seq_len.copy_(torch.from_numpy(inp["seq_len"]))
     got, trip, derr = _noalloc(dc, w)
     assert derr == 0 and trip == int(inp["seq_len"].max())
+
+
+# float32 H = 1024, I = 1024: the buffers of 4896 rows leave 308 096 bytes of
+# the scratch array, the chip-wide forward's ring and flags take 264 KB of it;
+# 4905 rows leave 127 836.  bfloat16 H = 96, I = 32, B = 8: 9673 steps leave
+# less than the XCD-local ring's 196 608 bytes.
+FORMS = [
+    (W("noalloc_bf16_h96", B=9, I=16, H=96, T_max=7, dtype="bf16", len_lo=0, len_hi=7, random_state=True,
+       seed=303), None),
+    (W("noalloc_bf16_h1056", B=40, I=24, H=1056, T_max=5, dtype="bf16", len_lo=0, len_hi=5, random_state=True,
+       seed=304), None),
+    (W("noalloc_f32_h1024_fits", B=16, I=1024, H=1024, T_max=306, dtype="f32", len_lo=1, len_hi=5,
+       random_state=True, seed=305), None),
+    (W("noalloc_f32_h1024_no_ring", B=15, I=1024, H=1024, T_max=327, dtype="f32", len_lo=1, len_hi=5,
+       random_state=True, seed=306), "grid"),
+    (W("noalloc_bf16_h96_no_ring", B=8, I=32, H=96, T_max=9673, dtype="bf16", len_lo=1, len_hi=6,
+       random_state=True, seed=307), "grid"),
+]
+
+
+@pytest.mark.parametrize("w,loops", FORMS, ids=[w.name for w, _ in FORMS])
+def test_noalloc_takes_the_plans_loops_while_the_exchange_arrays_fit(w, loops, monkeypatch):
+    """Bitwise the plan's forward in the loop form the scratch array leaves
+    room for (None: the plan's own).  The chip-wide and the grid-barrier loops
+    sum the recurrent product in different orders, so that the two differ; the
+    three k-steps of H = 96 are summed in the same order by either form."""
+    monkeypatch.delenv("LSTMLOOP_LOOPS", raising=False)
+    say(f"[noalloc] {w.name}")
+    inp = wl.generate(w)
+    dc = DeviceCase(inp, w.H, w.I, w.layers, w.dtype)
+    got, trip, derr = _noalloc(dc, w)
+    assert derr == 0 and trip == int(inp["seq_len"].max())
+    own, _ = _plan_fwd(dc)
+    monkeypatch.setenv("LSTMLOOP_LOOPS", "grid")
+    grid, _ = _plan_fwd(dc)
+    same, other = (grid, own) if loops else (own, grid)
+    for k in FWD_KEYS:
+        np.testing.assert_array_equal(got[k], same[k], err_msg=k)
+    if w.H > 96:
+        assert not np.array_equal(got["hT"], other["hT"])
+    if w.T_max < 1000:
+        errs, bad = compare(got, oracle_reference(inp, w.layers, w.dtype), TOL[w.dtype], keys=FWD_KEYS)
+        say(f"    errors vs oracle {errs}")
+        assert not bad, bad
