@@ -304,13 +304,16 @@ __global__ __launch_bounds__(256) void permute_um_kernel(const T* __restrict__ W
 // reads 16 bytes and writes 4 per step, HBM-bound, coalesced over the units).
 // It replaces a fifth of the swapped bytes: f32 H = 512, B = 64, T = 2000
 // through a ring of four 32-step chunks, 55.6 -> 46.9 ms a training step.
-__global__ __launch_bounds__(256) void rebuild_c_kernel(const float* __restrict__ gates, const float* __restrict__ c_in,
-                                                        const int* __restrict__ active, const int* __restrict__ perm,
-                                                        int B, int H, int t0, int t1, float* __restrict__ c) {
+// c_in: c entering the chunk, in the caller's row order (perm) or, without
+// perm, in length order; it may be c's own first row (each thread reads its
+// element before it writes there).
+__global__ __launch_bounds__(256) void rebuild_c_kernel(const float* __restrict__ gates, const float* c_in,
+                                                        const int* __restrict__ perm, const int* __restrict__ active,
+                                                        int B, int H, int t0, int t1, float* c) {
   const long i = blockIdx.x * 256L + threadIdx.x;
   if (i >= (long)B * H) return;
   const int r = (int)(i / H), u = (int)(i - (long)r * H);
-  float v = c_in ? c_in[(long)perm[r] * H + u] : 0.f;
+  float v = c_in ? c_in[(long)(perm ? perm[r] : r) * H + u] : 0.f;
   for (int t = t0; t < t1; ++t) {
     if (r >= active[t]) return;   // (rows are in length order: finished for good)
     const long row = (long)(t - t0) * B + r;
@@ -320,10 +323,10 @@ __global__ __launch_bounds__(256) void rebuild_c_kernel(const float* __restrict_
   }
 }
 
-hipError_t launch_rebuild_c(const float* gates, const float* c_in, const int* active, const int* perm, int B, int H,
+hipError_t launch_rebuild_c(const float* gates, const float* c_in, const int* perm, const int* active, int B, int H,
                             int t0, int t1, float* c, hipStream_t s) {
   const long n = (long)B * H;
-  hipLaunchKernelGGL(rebuild_c_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, gates, c_in, active, perm,
+  hipLaunchKernelGGL(rebuild_c_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, gates, c_in, perm, active,
                      B, H, t0, t1, c);
   return hipGetLastError();
 }

@@ -429,9 +429,10 @@ hipError_t launch_sum_scatter_rows(const float* ws, int nsl, long stride, const 
 hipError_t launch_zero_u32(unsigned* p, int n, hipStream_t s);
 // c of steps [t0, t1) rebuilt from the gates (rows (t - t0) B + r of `gates`
 // [.., 4H], unit u's i, f, g, o at 4u) and the entering state c_in [B, H]
-// (original order, or NULL), into rows (t - t0) B + r of c [.., H]: the same
-// operations as the forward loop's, so the same bits.
-hipError_t launch_rebuild_c(const float* gates, const float* c_in, const int* active, const int* perm, int B, int H,
+// (NULL: zeros; in the caller's row order if perm is given, else in length
+// order, and then possibly c's first row), into rows (t - t0) B + r of
+// c [.., H]: the same operations as the forward loop's, so the same bits.
+hipError_t launch_rebuild_c(const float* gates, const float* c_in, const int* perm, const int* active, int B, int H,
                             int t0, int t1, float* c, hipStream_t s);
 
 // Sustained matrix-core rate of the device (TFLOP/s), for reports: the 16x16

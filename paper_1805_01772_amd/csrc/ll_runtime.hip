@@ -219,7 +219,6 @@ struct ll_plan {
   // ... and W_h in unit-major order and, with xflags_b, the gradient loop's flags
   bool bwd_prepared = false;
   std::vector<hipEvent_t> ev_d2h, ev_h2d;   // per (layer, slot)
-  float* c_enter = nullptr;    // spill: c entering each chunk, [layers][nchunks][B, H] (original order)
   float* carry = nullptr;      // [4][B, H]: h, c (forward) / dh, dc (backward) between chunks
   float* db_state = nullptr;   // per-thread db sums between backward chunks
   float* db_part = nullptr;
@@ -378,7 +377,7 @@ void free_plan_memory(ll_plan* p) {
                   p->dyc, p->xring, p->xflags, p->db_part, p->ws, p->carry, p->db_state,
                   p->xring2, p->DZ2, p->dyx, p->db_part2, p->cring, p->cpart, p->cflags,
                   p->gslot, p->rc_inmap, p->rc_prevmap, p->rc_bias, p->sx, p->guards, p->Wum[0],
-                  p->Wum[1], p->prevc, p->HI, p->ntrip, p->tn_flags, p->xflags_b, p->c_enter};
+                  p->Wum[1], p->prevc, p->HI, p->ntrip, p->tn_flags, p->xflags_b};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   for (float* h : p->host_stack)
@@ -797,7 +796,6 @@ ll_status plan_layout(ll_plan* p, bool fwd_only, Take&& take) {
     ALLOC(p->rc_prevmap, sizeof(int) * cap, "recomputation row maps");
     ALLOC(p->rc_bias, sizeof(float) * L * 4 * H, "saved bias");
   }
-  if (p->spill) ALLOC(p->c_enter, sizeof(float) * L * (long)p->nchunks * B * H, "chunk entering states");
   if (p->spill || p->recompute) {
     ALLOC(p->carry, sizeof(float) * 4 * B * H, "chunk carry");
     ALLOC(p->db_state, sizeof(float) * 8 * 32 * 512 * 4, "db state");
@@ -951,9 +949,7 @@ ll_status ll_plan_create(const ll_desc* desc, int device, ll_plan** out) {
   }
   const int64_t stack_dev = p->spill ? (int64_t)sizeof(float) * p->nslots * p->slot_floats
                                      : (int64_t)sizeof(float) * p->M * cap * (p->recompute || p->G == 1 ? 1 : 5) * H;
-  // (the swapped chunks' c is rebuilt from c entering each chunk: 4/5 of the
-  // bytes cross the host link)
-  p->stack_device_bytes = (p->spill ? (int64_t)sizeof(float) * L * p->nchunks * B * H : 0) + (int64_t)L * (stack_dev + (int64_t)es * (cap + (p->recompute ? B : 0)) * H);
+  p->stack_device_bytes = (int64_t)L * (stack_dev + (int64_t)es * (cap + (p->recompute ? B : 0)) * H);
   if (p->recompute) p->stack_device_bytes += (int64_t)sizeof(float) * p->rc_steps * B * 4 * H;
   p->stack_host_bytes =
       p->spill ? (int64_t)L * (int64_t)sizeof(float) * std::max(0, p->nchunks - p->nslots) * p->slot_floats : 0;
@@ -1340,10 +1336,7 @@ ll_status enqueue_fwd(ll_plan* p, hipStream_t s, const void* x, const int32_t* s
         xa.h0 = hin;
         xa.c0 = cin;
         xa.hT = last ? hout : p->carry;
-        // (spill: c entering the next chunk stays, the swapped-in chunks'
-        // c is rebuilt from it)
-        float* const cnext = p->spill ? p->c_enter + ((long)l * nch + k + 1) * B * H : p->carry + (long)B * H;
-        xa.cT = last ? cout : cnext;
+        xa.cT = last ? cout : p->carry + (long)B * H;
         LL_HIP(chained_loop_launch(p->device, s, [&] { return ll::x_launch(p->xk.fwd, xa, 256, p->xk.lds_fwd, s); }));
         tend(p, s, LL_STAGE_FWD_LOOP, ev);
         if (p->spill && save && k < nch - p->nslots) {   // evicted later: swap it out on the copy stream
@@ -1351,13 +1344,19 @@ ll_status enqueue_fwd(ll_plan* p, hipStream_t s, const void* x, const int32_t* s
           // (two copy streams: the next chunk's copy is queued while this one runs)
           hipStream_t cs = (k & 1) ? p->cstream2 : p->cstream;
           LL_HIP(hipStreamWaitEvent(cs, p->ev_compute, 0));
-          const long gate_floats = (long)C * B * 4 * H;   // (c is rebuilt, not moved)
-          LL_HIP(copy_on_dma_engine(p->host_stack[l] + (long)k * p->slot_floats, p->stack[l] + slot * gate_floats,
-                                    sizeof(float) * gate_floats, hipMemcpyDeviceToHost, cs));
+          // the gates, then c of the chunk's last step: the next chunk's c is
+          // rebuilt from it (rows in length order; those that ended in this
+          // chunk are not read)
+          const long gate_floats = (long)C * B * 4 * H, row_floats = (long)B * H;
+          float* const host = p->host_stack[l] + (long)k * p->slot_floats;
+          LL_HIP(copy_on_dma_engine(host, p->stack[l] + slot * gate_floats, sizeof(float) * gate_floats,
+                                    hipMemcpyDeviceToHost, cs));
+          LL_HIP(copy_on_dma_engine(host + gate_floats, xa.cstk + (slot * (long)C + C - 1) * row_floats,
+                                    sizeof(float) * row_floats, hipMemcpyDeviceToHost, cs));
           LL_HIP(hipEventRecord(p->ev_d2h[l * p->nslots + slot], cs));
         }
         hin = p->carry;
-        cin = cnext;
+        cin = p->carry + (long)B * H;
       }
       continue;
     }
@@ -2035,10 +2034,10 @@ ll_status enqueue_bwd(ll_plan* p, hipStream_t s, const float* dy, const float* d
       auto load_chunk = [&](int j) -> ll_status {
         if (!p->spill || j < 0 || j >= nch - R) return LL_OK;
         LL_HIP(hipStreamWaitEvent(s, p->ev_h2d[l * R + j % R], 0));
-        const float* cin = j > 0 ? p->c_enter + ((long)l * nch + j) * B * H : xa.c0;
         const long rows = (long)C * B;
-        LL_HIP(ll::launch_rebuild_c(p->stack[l] + (j % R) * rows * 4 * H, cin, p->active, p->perm, B, H, j * C,
-                                    std::min(d.T_max, (j + 1) * C), xa.cstk + (j % R) * rows * H, s));
+        float* const c = xa.cstk + (j % R) * rows * H;
+        LL_HIP(ll::launch_rebuild_c(p->stack[l] + (j % R) * rows * 4 * H, j > 0 ? c : xa.c0,
+                                    j > 0 ? nullptr : p->perm, p->active, B, H, j * C, (j + 1) * C, c, s));
         return LL_OK;
       };
       for (int k = nch - 1; k >= 0; --k) {
@@ -2066,9 +2065,14 @@ ll_status enqueue_bwd(ll_plan* p, hipStream_t s, const float* dy, const float* d
           LL_HIP(hipEventRecord(p->ev_compute, s));
           hipStream_t cs = (j & 1) ? p->cstream2 : p->cstream;
           LL_HIP(hipStreamWaitEvent(cs, p->ev_compute, 0));
-          const long gate_floats = (long)C * B * 4 * H;
-          LL_HIP(copy_on_dma_engine(p->stack[l] + (j % R) * gate_floats, p->host_stack[l] + (long)j * p->slot_floats,
-                                    sizeof(float) * gate_floats, hipMemcpyHostToDevice, cs));
+          // (c entering the chunk waits in the chunk's first row of c)
+          const long gate_floats = (long)C * B * 4 * H, row_floats = (long)B * H;
+          float* const host = p->host_stack[l] + (long)j * p->slot_floats;
+          LL_HIP(copy_on_dma_engine(p->stack[l] + (j % R) * gate_floats, host, sizeof(float) * gate_floats,
+                                    hipMemcpyHostToDevice, cs));
+          if (j > 0)
+            LL_HIP(copy_on_dma_engine(xa.cstk + (j % R) * (long)C * row_floats, host - p->slot_floats + gate_floats,
+                                      sizeof(float) * row_floats, hipMemcpyHostToDevice, cs));
           LL_HIP(hipEventRecord(p->ev_h2d[l * R + j % R], cs));
         }
       }

@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 from paper_1805_01772_amd import workloads as wl
+from paper_1805_01772_amd.lstmloop import Plan
 from paper_1805_01772_amd.runner import DeviceCase
 from _helpers import say
 
@@ -36,3 +37,15 @@ def test_swapped_stack_bitwise_at_chunk_edges(dtype, layers, B, H, T, C, monkeyp
         np.testing.assert_array_equal(outs[0][k], outs[1][k])
     for a, b in zip(outs[0]["dW"] + outs[0]["dbias"], outs[1]["dW"] + outs[1]["dbias"]):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("layers,C", [(1, 1), (2, 4)])
+def test_swapped_stack_stays_within_its_budget(layers, C):
+    """The plan's device stack is the budget's chunk slots and the h history,
+    whatever the number of chunks: nothing grows with T_max beside them."""
+    B, H, T, R = 16, 64, 200, 5
+    slots = R * C * B * 5 * H * 4
+    say(f"[spill] device bytes, {layers} layer(s), chunks of {C}")
+    with Plan(T, B, 32, H, layers=layers, dtype="f32", spill=1, spill_chunk_steps=C,
+              device_stack_budget_bytes=slots) as plan:
+        assert plan.stack_bytes()[0] == layers * (slots + T * B * H * 4)
