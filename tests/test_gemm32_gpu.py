@@ -147,3 +147,26 @@ def test_float32_dw_error(cell, T, B, I, H):
         err = ((got - ref).norm() / ref.norm()).item()
         say(f"[gemm32] {cell} dW_{half} over {T * B} rows: relative error {err:.2e}")
         assert err < (2.8e-7 ** 2 + 2.0e-7 ** 2 + 2.8e-7 ** 2 + 2e-7 ** 2) ** 0.5
+
+
+@pytest.mark.parametrize("cell", ["lstm", "gru"])
+def test_float32_dw_past_two_gib_takes_the_transposes(cell):
+    """H = 512, B = 64, T_max = 4096: the dz rows of the row capacity reach
+    2 GiB, past the 32-bit offsets of the product over rows, so the plan takes
+    the gather-transposes and the split-K product of the copies (the GRU's in
+    three parts).  Short lengths; every output against the oracle."""
+    w = W(f"g32_{cell}_b64_i16_h512_t4096", B=64, I=16, H=512, T_max=4096, dtype="f32", len_lo=0, len_hi=5,
+          cell=cell, random_state=True, seed=421)
+    say(f"[gemm32] {w.name}")
+    inp = wl.generate(w)
+    dc = DeviceCase(inp, w.H, w.I, 1, "f32", cell=cell)
+    plan = dc.plan()
+    assert plan.geometry()["dw_in_place"] == [False]
+    dc.fwd(plan)
+    dc.bwd(plan)
+    assert plan.status_sync() == 0
+    res = dc.results()
+    plan.close()
+    errs, bad = compare(res, oracle_reference(inp, 1, "f32", cell=cell), TOL["f32"])
+    say(f"    errors {errs}")
+    assert not bad, bad
