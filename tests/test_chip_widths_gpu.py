@@ -5,10 +5,12 @@ layers, one to four row tiles per XCD.  Chip-wide loops over their whole
 range: widths between the powers of two (odd counts of 32 units: shares of the reduction of unequal
 length, a last gradient column group that is half filled), and batches at the
 edges of the row groups (32) and of the waves' shares (64, 128, 256)."""
+import numpy as np
 import pytest
 
 from paper_1805_01772_amd import workloads as wl
 from paper_1805_01772_amd.lstmloop import LL_EUNSUPPORTED, LoopError, Plan
+from paper_1805_01772_amd.runner import DeviceCase
 from _helpers import TOL, compare, oracle_reference, say
 from test_parity_gpu import run_case
 
@@ -76,3 +78,26 @@ def test_odd_widths_refused_for_other_bodies_and_policies(kw):
     with pytest.raises(LoopError) as e:
         Plan(8, 4, 32, 96, dtype="bf16", **kw)
     assert e.value.status == LL_EUNSUPPORTED
+
+
+@pytest.mark.parametrize("dtype,wide,narrow,B", [("bf16", 2048, 1056, 40), ("f32", 768, 544, 20)])
+def test_wide_plan_runs_after_a_narrow_one_was_made(dtype, wide, narrow, B, monkeypatch):
+    """Two live plans of the same kernels whose LDS sizes differ: making the
+    narrower one takes nothing from the wider one (bitwise its own results)."""
+    monkeypatch.delenv("LSTMLOOP_LOOPS", raising=False)
+    say(f"[chip widths] {dtype} H = {wide} after H = {narrow}")
+    w = W("wide", B=B, I=8, H=wide, T_max=4, dtype=dtype, len_lo=1, len_hi=4, random_state=True, seed=351)
+    dc = DeviceCase(wl.generate(w), w.H, w.I, 1, dtype)
+    with dc.plan() as plan:
+        dc.fwd(plan)
+        dc.bwd(plan)
+        assert plan.status_sync() == 0
+        first = dc.results()
+        with Plan(4, B, 8, narrow, dtype=dtype) as other:
+            assert plan.geometry()["loops"] == other.geometry()["loops"] == "chip"
+            dc.fwd(plan)
+            dc.bwd(plan)
+            assert plan.status_sync() == 0
+    again = dc.results()
+    for k in ("y", "hT", "cT", "dx", "dh0", "dc0"):
+        np.testing.assert_array_equal(again[k], first[k], err_msg=k)
