@@ -156,9 +156,9 @@ typedef enum {
  *     plan's copy stream after the forward launch that filled it, and
  *     copied back once, ahead of the gradient launches that read it; the
  *     last R chunks never leave the device, so a budget that holds every
- *     chunk moves nothing.  Of a chunk only the gates i, f, g, o and c of its
- *     last step cross the host link: c_t is rebuilt from them with the forward
- *     loop's own operations.  R = device_stack_budget_bytes /
+ *     chunk moves nothing.  Of a chunk of at least 3 MiB only the gates i, f,
+ *     g, o and c of its last step cross the host link: c_t is rebuilt from
+ *     them with the forward loop's own operations.  R = device_stack_budget_bytes /
  *     (chunk_steps * B * 5H * 4), at least 3 (0 = 4); the results are
  *     bitwise those of spill = 0.
  *     Needs the XCD-local loops (see ll_plan_geometry); otherwise

@@ -69,6 +69,14 @@ long round_up(long v, long m) { return (v + m - 1) / m * m; }
 // fence left the GPU idle for several microseconds).
 constexpr unsigned kOrderEventFlags = hipEventDisableTiming | hipEventDisableSystemFence;
 
+// Swapped chunks of at least this many bytes leave c behind and rebuild it
+// (a fifth less over the host link); below, two more copies and a launch a
+// chunk cost more than they save.  Training steps of 200 steps, B = 24, whole
+// slots against rebuilt c: H = 512, 2.0 MB f32 2.93 and 3.10 ms, bf16 2.51 and
+// 2.63; 3.9 MB f32 2.28 and 2.33, bf16 1.95 and 1.75; 7.9 MB f32 1.93 and
+// 1.97, bf16 1.44 and 1.33; B = 64, 21 MB f32 14.1 and 12.2 (600 steps).
+constexpr long kRebuildSlotBytes = 3L << 20;
+
 // Loop launches of every plan on one device form one chain: each starts
 // after the previous one (whatever plan or stream enqueued it) has
 // completed.  The loops need all compute units co-resident, so two of them
@@ -193,6 +201,7 @@ struct ll_plan {
   bool spill = false;
   int chunk_steps = 0, nslots = 1, nchunks = 1;
   long slot_floats = 0;
+  bool c_rebuilt = false;      // c of the swapped chunks does not cross the host link
   float* host_stack[2] = {nullptr, nullptr};
   hipStream_t cstream = nullptr;
   hipStream_t cstream2 = nullptr;   // chunks alternate between the two copy streams
@@ -603,6 +612,7 @@ ll_status plan_configure(ll_plan* p, const ll_desc* desc, int device, const hipD
     const long slot_bytes = p->slot_floats * (long)sizeof(float);
     long r = desc->device_stack_budget_bytes > 0 ? desc->device_stack_budget_bytes / slot_bytes : 4;
     p->nslots = (int)std::max(3L, std::min(r, (long)p->nchunks));
+    p->c_rebuilt = slot_bytes >= kRebuildSlotBytes;
   }
   if (desc->recompute) {
     if (!p->xmode) {
@@ -1072,7 +1082,7 @@ ll::XLoopArgs x_common(const ll_plan* p) {
   const bool five = p->G == 4 || p->G == 3;
   a.sld = a.csld = five ? 5 * p->d.H : p->d.H;
   a.sgates = five ? 1 : 0;
-  if (p->spill) {            // ring of chunk slots: the gates of every slot, then c of every slot
+  if (p->c_rebuilt) {        // ring of chunk slots: the gates of every slot, then c of every slot
     a.sld = 4 * p->d.H;
     a.csld = p->d.H;
   } else if (p->recompute) { // c only
@@ -1085,7 +1095,7 @@ ll::XLoopArgs x_common(const ll_plan* p) {
 // c of the saved stack (see x_common).
 float* c_of_stack(const ll_plan* p, float* stack) {
   if (!stack) return nullptr;
-  if (p->spill) return stack + (long)p->nslots * p->chunk_steps * p->d.B * 4 * p->d.H;
+  if (p->c_rebuilt) return stack + (long)p->nslots * p->chunk_steps * p->d.B * 4 * p->d.H;
   return stack + (p->recompute || p->G == 1 ? 0 : 4 * p->d.H);
 }
 
@@ -1344,15 +1354,16 @@ ll_status enqueue_fwd(ll_plan* p, hipStream_t s, const void* x, const int32_t* s
           // (two copy streams: the next chunk's copy is queued while this one runs)
           hipStream_t cs = (k & 1) ? p->cstream2 : p->cstream;
           LL_HIP(hipStreamWaitEvent(cs, p->ev_compute, 0));
-          // the gates, then c of the chunk's last step: the next chunk's c is
-          // rebuilt from it (rows in length order; those that ended in this
-          // chunk are not read)
-          const long gate_floats = (long)C * B * 4 * H, row_floats = (long)B * H;
+          // the whole slot, or the gates and then c of the chunk's last step:
+          // the next chunk's c is rebuilt from it (rows in length order; those
+          // that ended in this chunk are not read)
+          const long row_floats = (long)B * H, moved = p->c_rebuilt ? C * 4 * row_floats : p->slot_floats;
           float* const host = p->host_stack[l] + (long)k * p->slot_floats;
-          LL_HIP(copy_on_dma_engine(host, p->stack[l] + slot * gate_floats, sizeof(float) * gate_floats,
-                                    hipMemcpyDeviceToHost, cs));
-          LL_HIP(copy_on_dma_engine(host + gate_floats, xa.cstk + (slot * (long)C + C - 1) * row_floats,
-                                    sizeof(float) * row_floats, hipMemcpyDeviceToHost, cs));
+          LL_HIP(copy_on_dma_engine(host, p->stack[l] + slot * moved, sizeof(float) * moved, hipMemcpyDeviceToHost,
+                                    cs));
+          if (p->c_rebuilt)
+            LL_HIP(copy_on_dma_engine(host + moved, xa.cstk + (slot * (long)C + C - 1) * row_floats,
+                                      sizeof(float) * row_floats, hipMemcpyDeviceToHost, cs));
           LL_HIP(hipEventRecord(p->ev_d2h[l * p->nslots + slot], cs));
         }
         hin = p->carry;
@@ -2034,6 +2045,7 @@ ll_status enqueue_bwd(ll_plan* p, hipStream_t s, const float* dy, const float* d
       auto load_chunk = [&](int j) -> ll_status {
         if (!p->spill || j < 0 || j >= nch - R) return LL_OK;
         LL_HIP(hipStreamWaitEvent(s, p->ev_h2d[l * R + j % R], 0));
+        if (!p->c_rebuilt) return LL_OK;
         const long rows = (long)C * B;
         float* const c = xa.cstk + (j % R) * rows * H;
         LL_HIP(ll::launch_rebuild_c(p->stack[l] + (j % R) * rows * 4 * H, j > 0 ? c : xa.c0,
@@ -2066,12 +2078,12 @@ ll_status enqueue_bwd(ll_plan* p, hipStream_t s, const float* dy, const float* d
           hipStream_t cs = (j & 1) ? p->cstream2 : p->cstream;
           LL_HIP(hipStreamWaitEvent(cs, p->ev_compute, 0));
           // (c entering the chunk waits in the chunk's first row of c)
-          const long gate_floats = (long)C * B * 4 * H, row_floats = (long)B * H;
+          const long row_floats = (long)B * H, moved = p->c_rebuilt ? C * 4 * row_floats : p->slot_floats;
           float* const host = p->host_stack[l] + (long)j * p->slot_floats;
-          LL_HIP(copy_on_dma_engine(p->stack[l] + (j % R) * gate_floats, host, sizeof(float) * gate_floats,
+          LL_HIP(copy_on_dma_engine(p->stack[l] + (j % R) * moved, host, sizeof(float) * moved,
                                     hipMemcpyHostToDevice, cs));
-          if (j > 0)
-            LL_HIP(copy_on_dma_engine(xa.cstk + (j % R) * (long)C * row_floats, host - p->slot_floats + gate_floats,
+          if (p->c_rebuilt && j > 0)
+            LL_HIP(copy_on_dma_engine(xa.cstk + (j % R) * C * row_floats, host - p->slot_floats + moved,
                                       sizeof(float) * row_floats, hipMemcpyHostToDevice, cs));
           LL_HIP(hipEventRecord(p->ev_h2d[l * R + j % R], cs));
         }

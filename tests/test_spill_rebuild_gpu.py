@@ -1,6 +1,6 @@
 """GPU test of the c values rebuilt for swapped-in chunks: a swapped stack
-gives the resident stack's results bitwise at the edges of the chunks (a
-chunk of one step, a last chunk cut short, rows that end on a chunk's first
+gives the resident stack's results bitwise, c rebuilt or swapped with the
+gates, at the edges of the chunks (a chunk of one step, a last chunk cut short, rows that end on a chunk's first
 and last step, rows that never start, random entering states in two layers)."""
 import numpy as np
 import pytest
@@ -14,7 +14,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype,layers,B,H,T,C", [("f32", 1, 17, 64, 13, 1), ("f32", 2, 20, 32, 31, 4),
-                                                  ("bf16", 1, 33, 64, 24, 6), ("bf16", 1, 130, 128, 22, 3)])
+                                                  ("bf16", 1, 33, 64, 24, 6), ("bf16", 1, 130, 128, 22, 3),
+                                                  # either side of 3 MiB a chunk, from where c is rebuilt
+                                                  ("f32", 1, 64, 512, 23, 4), ("f32", 2, 64, 512, 23, 5),
+                                                  ("bf16", 1, 160, 1024, 11, 1), ("bf16", 2, 80, 512, 17, 4)])
 def test_swapped_stack_bitwise_at_chunk_edges(dtype, layers, B, H, T, C, monkeypatch):
     monkeypatch.setenv("LSTMLOOP_WAVEFRONT", "off")
     w = wl.Workload("rebuild", B=B, I=24, H=H, T_max=T, dtype=dtype, layers=layers, len_lo=0, len_hi=T,
