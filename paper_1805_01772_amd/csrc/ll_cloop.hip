@@ -16,7 +16,7 @@
 // Inside a work-group every wave runs the recurrence of its own rows alone:
 // the batch is cut into groups of 32 rows, wave w takes row group w % RW and
 // share w / RW of the work-group's reduction (RW KW = 8; c_kernels says how
-// many and why).  No barrier stands in a
+// many and why, and where the float32 forward has sixteen waves).  No barrier stands in a
 // step: the shares meet in LDS behind flags (forward) or as partial products
 // of the group, like the KG slices (gradient), and the waves of a SIMD hide
 // each other's waits.  Measured: the forward loop with a reduction split over
@@ -266,7 +266,7 @@ __device__ __forceinline__ int group_len(const CLoopArgs& a, int rg, int T_eff) 
 // Forward loop, chip-wide.  Work-group wg owns KPC hidden units (8 bf16, 4
 // f32): the 16 NT gate columns of the whole reduction.  The weights are the
 // first matrix-core operand, rows 4 unit + gate, and the 32 batch rows of a
-// wave the columns, so a result register quad is the four gates of one
+// wave (RTL row tiles of 16: one for at most 16 rows) the columns, so a result register quad is the four gates of one
 // (row, unit): the cell runs where the product ends.  One product step for
 // lane 16 q + l: rows l of the two row tiles, units NT q .. NT q + NT - 1.
 // ---------------------------------------------------------------------------
@@ -274,45 +274,50 @@ __device__ __forceinline__ int group_len(const CLoopArgs& a, int rg, int T_eff) 
 // share is padded to whole bodies: float32's short shares (KW >= 4) take 4,
 // for there the products of the padding cost more than the loads in flight
 // give (H = 640, B = 64 11.2 us a step with 8, 10.4 with 4; H = 1024 equal;
-// the longer shares of B = 128, H = 1024 17.3 with 8, 19.9 with 4).
-template <typename T, int KW>
-constexpr int cfwd_unroll() { return sizeof(T) == 4 && KW >= 4 ? 4 : 8; }
-template <typename T, int KW_>
+// the longer shares of B = 128, H = 1024 17.3 with 8, 19.9 with 4), and so do
+// sixteen waves, which have 128 registers each.
+template <typename T, int KW, int NW>
+constexpr int cfwd_unroll() { return sizeof(T) == 4 && (KW >= 4 || NW == 16) ? 4 : 8; }
+template <typename T, int KW_, int RTL_, int NW_ = 8>
 struct CFwd {
   static constexpr int KPC = Op<T>::kPerChunk;
-  static constexpr int KW = KW_;
-  static constexpr int RW = CNW / KW;            // row groups
+  static constexpr int KW = KW_, RTL = RTL_;     // shares; row tiles of a row group
+  static constexpr int NW = NW_;
+  static constexpr int RW = NW / KW;             // row groups
   static constexpr int NT = KPC / 4;             // weight tiles: units per lane and row
-  static constexpr int RT = KW == 1 ? 2 : 1;     // row tiles of a cell wave
-  static constexpr int NCF = KW == 1 ? 1 : 2;    // cell waves (exchange flags) per row group
+  static constexpr int NCF = KW == 1 ? 1 : RTL;  // cell waves (exchange flags) per row group
+  static constexpr int RT = RTL / NCF;           // row tiles of a cell wave
 };
 // LDS of the forward kernel: weights, the shares' partial products on their
 // way to the cell waves, the flags of that hand-over.
-template <typename T, int KW>
+template <typename T, int KW, int NW>
 __host__ __device__ constexpr int cfwd_weight_chunks(int KS) {
-  return KW * c_share<T>(KS, KW, cfwd_unroll<T, KW>()) * CFwd<T, KW>::NT * 64;
+  return KW * c_share<T>(KS, KW, cfwd_unroll<T, KW, NW>()) * CFwd<T, KW, 2, NW>::NT * 64;
 }
-template <typename T, int KW>
+template <typename T, int KW, int NW>
 __host__ __device__ constexpr int cfwd_part_chunks() {
-  return CFwd<T, KW>::RW * 2 * (KW - 1) * CFwd<T, KW>::NT * 64;
+  return CFwd<T, KW, 2, NW>::RW * 2 * (KW - 1) * CFwd<T, KW, 2, NW>::NT * 64;
 }
-template <typename T, int KW>
+template <typename T, int KW, int NW>
 constexpr size_t cfwd_lds(int H) {
   const int KS = H / (4 * Op<T>::kPerChunk);
-  return (size_t)(cfwd_weight_chunks<T, KW>(KS) + cfwd_part_chunks<T, KW>()) * 16 + (CNW + 2 * CNW) * 4;
+  return (size_t)(cfwd_weight_chunks<T, KW, NW>(KS) + cfwd_part_chunks<T, KW, NW>()) * 16 + 3 * NW * 4;
 }
 
 // Wait until the n <= 256 flags of the range are all >= need (n % 4 == 0, 16
-// bytes per lane and poll).
+// bytes per lane and poll).  A lane whose flags are there asks no more: every
+// wave of the chip polls, beside the ring's loads (f32 H = 1024, inference of
+// 40 steps, B = 64 643 -> 606 us, B = 128 810 -> 774; bf16 equal).
 __device__ __forceinline__ void wait_quads(const CLoopArgs& a, __amdgpu_buffer_rsrc_t flags, int n, unsigned need) {
   const int lane = threadIdx.x & 63;
-  const bool mine = lane * 4 < n;
+  bool mine = lane * 4 < n;
   unsigned long long t0 = 0;
   unsigned polls = 0;
   while (true) {
     const uint4 f = ld_chunk_l2(flags, mine ? (unsigned)(lane * 16) : kOOB);
     const bool late = mine && (f.x < need || f.y < need || f.z < need || f.w < need);
     if (__builtin_amdgcn_ballot_w64(late) == 0) break;
+    mine = late;
     if (polls == 0) t0 = wall_clock64();
     __builtin_amdgcn_s_sleep(1);
     asm volatile("" ::: "memory");   // (every poll loads again)
@@ -358,16 +363,18 @@ __device__ __forceinline__ void set_lds(unsigned* flag, unsigned value) {
 // work-groups of an XCD read the same freshly written blocks and start
 // apart).  Even and odd k-steps sum apart (half the length of a rounding
 // chain).
-template <typename T, int NT, int U>
+template <typename T, int NT, int RTL, int U>
 __device__ __forceinline__ void cfwd_product(__amdgpu_buffer_rsrc_t rs, const uint4* w, int ng, int rot,
-                                             f32x4 (&acc)[NT][2]) {
+                                             f32x4 (&acc)[NT][RTL]) {
   const int lane = threadIdx.x & 63;
-  uint4 b[U][2], wv[2][2 * NT];
-  f32x4 s[2][NT][2];
+  uint4 b[U][RTL], wv[2][2 * NT];
+  f32x4 s[2][NT][RTL];
 #pragma unroll
   for (int k = 0; k < 2; ++k)
 #pragma unroll
-    for (int n = 0; n < NT; ++n) s[k][n][0] = s[k][n][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+      for (int rt = 0; rt < RTL; ++rt) s[k][n][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
   const uint4* wl = w + lane;
   auto rd = [&](uint4 (&v)[2 * NT], int g, int c) {   // weights of k-steps 2c, 2c + 1 of group g
 #pragma unroll
@@ -377,7 +384,7 @@ __device__ __forceinline__ void cfwd_product(__amdgpu_buffer_rsrc_t rs, const ui
 #pragma unroll
   for (int i = 0; i < U; ++i)
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt)
+    for (int rt = 0; rt < RTL; ++rt)
       b[i][rt] = ld_chunk_l2(rs, (unsigned)(((cur * U + i) * 2 + rt) << 10) + lane * 16);
   rd(wv[0], cur, 0);
   for (int left = ng; left > 0; --left) {
@@ -392,10 +399,10 @@ __device__ __forceinline__ void cfwd_product(__amdgpu_buffer_rsrc_t rs, const ui
 #pragma unroll
         for (int n = 0; n < NT; ++n)
 #pragma unroll
-          for (int rt = 0; rt < 2; ++rt) s[k][n][rt] = Mfma<T>::step(wv[c & 1][k * NT + n], b[i][rt], s[k][n][rt]);
+          for (int rt = 0; rt < RTL; ++rt) s[k][n][rt] = Mfma<T>::step(wv[c & 1][k * NT + n], b[i][rt], s[k][n][rt]);
         // (the last group asks past the range: no traffic)
 #pragma unroll
-        for (int rt = 0; rt < 2; ++rt)
+        for (int rt = 0; rt < RTL; ++rt)
           b[i][rt] = ld_chunk_l2(rs, left > 1 ? (unsigned)(((nxt * U + i) * 2 + rt) << 10) + lane * 16 : kOOB);
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -405,12 +412,12 @@ __device__ __forceinline__ void cfwd_product(__amdgpu_buffer_rsrc_t rs, const ui
 #pragma unroll
   for (int n = 0; n < NT; ++n)
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) acc[n][rt] = s[0][n][rt] + s[1][n][rt];
+    for (int rt = 0; rt < RTL; ++rt) acc[n][rt] = s[0][n][rt] + s[1][n][rt];
 }
 
-template <typename T, int KW>
-__global__ __launch_bounds__(CNT, 1) void cfwd_kernel(CLoopArgs a) {
-  using S = CFwd<T, KW>;
+template <typename T, int KW, int RTL, int NW>
+__global__ __launch_bounds__(64 * NW, 1) void cfwd_kernel(CLoopArgs a) {
+  using S = CFwd<T, KW, RTL, NW>;
   constexpr int KPC = S::KPC, RW = S::RW, NT = S::NT, RT = S::RT, NCF = S::NCF;
   extern __shared__ uint4 lds[];
   const int H = a.H, B = a.B, RGN = a.RGN;
@@ -421,16 +428,16 @@ __global__ __launch_bounds__(CNT, 1) void cfwd_kernel(CLoopArgs a) {
   }
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
   const int q = lane >> 4, l16 = lane & 15;
-  const int KS = H / (4 * KPC), KSP = c_share<T>(KS, KW, cfwd_unroll<T, KW>());   // k-steps; of a share, padded
+  const int KS = H / (4 * KPC), KSP = c_share<T>(KS, KW, cfwd_unroll<T, KW, NW>());   // k-steps; of a share, padded
   const long G4 = 4L * H, H5 = 5L * H;
-  uint4* parts = lds + cfwd_weight_chunks<T, KW>(KS);
-  unsigned* pf = reinterpret_cast<unsigned*>(parts + cfwd_part_chunks<T, KW>());   // [wave]: partials stored
-  unsigned* rf = pf + CNW;                                                         // [row group][row tile]: read
-  if (tid < 3 * CNW) pf[tid] = 0u;
+  uint4* parts = lds + cfwd_weight_chunks<T, KW, NW>(KS);
+  unsigned* pf = reinterpret_cast<unsigned*>(parts + cfwd_part_chunks<T, KW, NW>());   // [wave]: partials stored
+  unsigned* rf = pf + NW;                                                          // [row group][row tile]: read
+  if (tid < 3 * NW) pf[tid] = 0u;
   {
     // weights: row m of tile n is gate m % 4 of unit NT (m / 4) + n
     const T* WT = reinterpret_cast<const T*>(a.W) + a.woff;
-    for (int i = tid; i < KW * KSP * NT * 64; i += CNT) {
+    for (int i = tid; i < KW * KSP * NT * 64; i += 64 * NW) {
       const int l = i & 63, m = l & 15, n = (i >> 6) % NT, kk = (i >> 6) / NT, sh = kk / KSP;
       const int ks = sh * KS / KW + kk - sh * KSP;
       lds[i] = ks < (sh + 1) * KS / KW
@@ -439,7 +446,10 @@ __global__ __launch_bounds__(CNT, 1) void cfwd_kernel(CLoopArgs a) {
     }
   }
   __syncthreads();
-  const int rg = wave % RW, kw = wave / RW;
+  // (sixteen waves: neighbours share a row group, so that five or six groups
+  // spread over the four SIMDs)
+  const int rg = NW == 16 ? wave / KW : wave % RW, kw = NW == 16 ? wave % KW : wave / RW;
+  auto wave_of = [&](int k) { return NW == 16 ? rg * KW + k : k * RW + rg; };
   if (rg >= RGN) return;
   // cells: row tiles rt0 .. rt0 + RT - 1, row l16 of each, units j .. j + NT - 1
   const bool cellw = kw < NCF;
@@ -497,18 +507,18 @@ __global__ __launch_bounds__(CNT, 1) void cfwd_kernel(CLoopArgs a) {
       for (int n = 0; n < NT; ++n) zc[e][n] = zx[e][n];
     load_zx(A_n, off_t + A_t);
     if (t > 0 && nks > 0) wait_quads(a, rfl, nfl, (unsigned)(t + 1));
-    f32x4 acc[NT][2];
-    cfwd_product<T, NT, cfwd_unroll<T, KW>()>(make_rsrc(reinterpret_cast<char*>(a.ring) + (((long)((t + 1) & 1) * RGN + rg) * KS + ks0) * 2048,
+    f32x4 acc[NT][RTL];
+    cfwd_product<T, NT, RTL, cfwd_unroll<T, KW, NW>()>(make_rsrc(reinterpret_cast<char*>(a.ring) + (((long)((t + 1) & 1) * RGN + rg) * KS + ks0) * 2048,
                                   (unsigned)nks << 11),
-                        w, KSP / cfwd_unroll<T, KW>(), wg >> 3, acc);
+                        w, KSP / cfwd_unroll<T, KW, NW>(), wg >> 3, acc);
     if constexpr (KW > 1) {
       // the shares meet in LDS: each stores its product of the row tiles that
       // are not its own (once their cell waves have read step t-1's), wave
       // kw < 2 adds those of row tile kw in share order
-      wait_lds(a, rf, rg * 2 + (lane & 1), lane < 2, (unsigned)t);
+      wait_lds(a, rf, rg * 2 + (lane & 1), lane < NCF, (unsigned)t);
       float4* p4 = reinterpret_cast<float4*>(parts);
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt)
+      for (int rt = 0; rt < RTL; ++rt)
         if (kw != rt)
 #pragma unroll
           for (int n = 0; n < NT; ++n)
@@ -520,10 +530,10 @@ __global__ __launch_bounds__(CNT, 1) void cfwd_kernel(CLoopArgs a) {
         A_t = A_n;
         continue;
       }
-      wait_lds(a, pf, (lane % KW) * RW + rg, lane < KW, (unsigned)(t + 1));
+      wait_lds(a, pf, wave_of(lane % KW), lane < KW, (unsigned)(t + 1));
 #pragma unroll
       for (int n = 0; n < NT; ++n) {
-        f32x4 v = rt0 ? acc[n][1] : acc[n][0];
+        f32x4 v = rt0 ? acc[n][RTL - 1] : acc[n][0];
 #pragma unroll
         for (int s = 0; s < KW - 1; ++s) {
           const float4 u = p4[(((rg * 2 + rt0) * (KW - 1) + s) * NT + n) * 64 + lane];
@@ -948,20 +958,21 @@ template hipError_t launch_c_prepare<bf16_t>(const float*, const int*, int, int,
 
 namespace {
 // KW, KWF: shares of the gradient's slices and of the forward's reduction
-template <typename T, int KW, int KWF>
+template <typename T, int KW, int KWF, int RTL = 2, int NW = 8>
 CKernels c_make(int H, int rgn) {
   constexpr int KGB = sizeof(T) == 2 ? 8 : 16;
   CKernels k{};
-  k.fwd = reinterpret_cast<const void*>(&cfwd_kernel<T, KWF>);
+  k.fwd = reinterpret_cast<const void*>(&cfwd_kernel<T, KWF, RTL, NW>);
   k.bwd = reinterpret_cast<const void*>(&cbwd_kernel<T, KGB, KW>);
-  k.lds_fwd = cfwd_lds<T, KWF>(H);
+  k.threads_fwd = 64 * NW;
+  k.lds_fwd = cfwd_lds<T, KWF, NW>(H);
   k.lds_bwd = (size_t)KW * c_share<T>(H / 32, KW) * 2048 + CNW * kScratch;
   k.rgn = rgn;
   k.kw = KW;
   k.cw = Op<T>::kPerChunk;
   k.nwg_fwd = H / k.cw;
   k.part_floats = 8L * rgn * 32 * KW * kPartFloats;
-  k.flag_words_fwd = 8 + rgn * 256 * CFwd<T, KWF>::NCF;
+  k.flag_words_fwd = 8 + rgn * 256 * CFwd<T, KWF, RTL, NW>::NCF;
   k.flag_words = std::max(k.flag_words_fwd, 8 + rgn * 256 * KW + 8 * rgn * 32 * KW);
   return k;
 }
@@ -977,13 +988,26 @@ CKernels c_make(int H, int rgn) {
 // 10.8, 13.1, 17.4; 96: 11.5, 17.5; only float32's long slices of one row
 // group are faster shared by four (H = 1024 16 rows: 13.0, 13.2, 11.5;
 // H = 768: 10.4, -, 10.5).
+//
+// Forward.  At most 16 rows leave the second row tile of the group out
+// (inference of 40 steps, B = 16: bf16 H = 2048 370 -> 325 us, H = 1056
+// 330 -> 278; f32 H = 1024 389 -> 327, H = 544 338 -> 275).  float32's five
+// or six row groups: eight waves of a group each would put two on one SIMD
+// and one on each of the others, at 6.8 us of matrix work a step (H = 1024);
+// sixteen, two to a group, spread it (H = 1024 B = 160 1221 -> 1163 us, 192
+// 1307 -> 1229; seven or eight groups are even either way: 224 1410 -> 1495).
+// bfloat16's products are a quarter as long and its weights and shares of two
+// exceed the LDS.
 template <typename T>
 CKernels c_kernels(int H, int B) {
   const int rgn = (B + 31) / 32;
   if (H % 32 || H < 64 || H > (sizeof(T) == 2 ? 2048 : 1024) || rgn < 1 || rgn > 8) return CKernels{};
-  if constexpr (sizeof(T) == 4)
-    if (rgn <= 1 && H > 768) return c_make<T, 4, 8>(H, rgn);
-  return rgn <= 1   ? c_make<T, 1, 8>(H, rgn)
+  if constexpr (sizeof(T) == 4) {
+    if (rgn <= 1 && H > 768) return B <= 16 ? c_make<T, 4, 8, 1>(H, rgn) : c_make<T, 4, 8>(H, rgn);
+    if (rgn == 5 || rgn == 6) return c_make<T, 1, 2, 2, 16>(H, rgn);
+  }
+  return B <= 16    ? c_make<T, 1, 8, 1>(H, rgn)
+         : rgn <= 1 ? c_make<T, 1, 8>(H, rgn)
          : rgn <= 2 ? c_make<T, 1, 4>(H, rgn)
          : rgn <= 4 ? c_make<T, 1, 2>(H, rgn)
                     : c_make<T, 1, 1>(H, rgn);
@@ -1006,15 +1030,15 @@ hipError_t c_setup(const CKernels& k, int* occ_fwd, int* occ_bwd) {
   if (e != hipSuccess) return e;
   e = hipFuncSetAttribute(k.bwd, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.lds_bwd);
   if (e != hipSuccess) return e;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(occ_fwd, k.fwd, CNT, k.lds_fwd);
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(occ_fwd, k.fwd, k.threads_fwd, k.lds_fwd);
   if (e != hipSuccess) return e;
   return hipOccupancyMaxActiveBlocksPerMultiprocessor(occ_bwd, k.bwd, CNT, k.lds_bwd);
 }
 
-hipError_t c_launch(const void* fn, const CLoopArgs& a, int nwg, size_t lds, hipStream_t s) {
+hipError_t c_launch(const void* fn, const CLoopArgs& a, int nwg, int threads, size_t lds, hipStream_t s) {
   CLoopArgs copy = a;
   void* kargs[] = {&copy};
-  return hipLaunchKernel(fn, dim3((unsigned)nwg), dim3(CNT), kargs, lds, s);
+  return hipLaunchKernel(fn, dim3((unsigned)nwg), dim3((unsigned)threads), kargs, lds, s);
 }
 
 }  // namespace ll

@@ -380,6 +380,7 @@ struct CKernels {
   size_t lds_fwd;
   size_t lds_bwd;
   int nwg_fwd;            // work-groups of the forward loop
+  int threads_fwd;        // threads of each
   int rgn;                // row groups of 32
   int kw;                 // gradient: waves that share a reduction slice
   int cw;                 // cell units per work-group
@@ -391,7 +392,7 @@ struct CKernels {
 template <typename T>
 CKernels c_kernels(int H, int B);
 hipError_t c_setup(const CKernels& k, int* occ_fwd, int* occ_bwd);
-hipError_t c_launch(const void* fn, const CLoopArgs& a, int nwg, size_t lds, hipStream_t s);
+hipError_t c_launch(const void* fn, const CLoopArgs& a, int nwg, int threads, size_t lds, hipStream_t s);
 // h0 rows (length order, operand type) into ring slot 1 and every flag and
 // rank counter of the launch to zero.
 template <typename T>

@@ -1390,7 +1390,7 @@ ll_status enqueue_fwd(ll_plan* p, hipStream_t s, const void* x, const int32_t* s
       ca.hT = hT + (long)l * B * H;
       ca.cT = cT + (long)l * B * H;
       ev = tbeg(p, s, LL_STAGE_FWD_LOOP);
-      LL_HIP(chained_loop_launch(p->device, s, [&] { return ll::c_launch(p->ck.fwd, ca, p->ck.nwg_fwd, p->ck.lds_fwd, s); }));
+      LL_HIP(chained_loop_launch(p->device, s, [&] { return ll::c_launch(p->ck.fwd, ca, p->ck.nwg_fwd, p->ck.threads_fwd, p->ck.lds_fwd, s); }));
       tend(p, s, LL_STAGE_FWD_LOOP, ev);
       continue;
     }
@@ -2109,7 +2109,7 @@ ll_status enqueue_bwd(ll_plan* p, hipStream_t s, const float* dy, const float* d
       ca.dh0 = dh0 ? dh0 + (long)l * B * H : nullptr;
       ca.dc0 = dc0 ? dc0 + (long)l * B * H : nullptr;
       ev = tbeg(p, s, LL_STAGE_BWD_LOOP);
-      LL_HIP(chained_loop_launch(p->device, s, [&] { return ll::c_launch(p->ck.bwd, ca, 256, p->ck.lds_bwd, s); }));
+      LL_HIP(chained_loop_launch(p->device, s, [&] { return ll::c_launch(p->ck.bwd, ca, 256, 512, p->ck.lds_bwd, s); }));
       tend(p, s, LL_STAGE_BWD_LOOP, ev);
     }
     ll::BwdLoopArgs a{};

@@ -31,6 +31,12 @@ CASES = [W(f"chipw_{dtype}_b{B}_i{I}_h{H}_t{T}_l{L}", B=B, I=I, H=H, T_max=T, dt
 CASES += [W(f"chipw_f32_b{B}_i8_h{H}_t{T}", B=B, I=8, H=H, T_max=T, dtype="f32", len_lo=0, len_hi=T,
             random_state=True, seed=seed)
           for seed, (B, H, T) in enumerate([(30, 768, 4), (5, 800, 5), (64, 1024, 4), (97, 896, 4)], start=361)]
+# the forward's single row tile up to 16 rows, float32's sixteen waves for five to seven row groups
+CASES += [W(f"chipw_{dtype}_b{B}_i8_h{H}_t{T}", B=B, I=8, H=H, T_max=T, dtype=dtype, len_lo=0, len_hi=T,
+            random_state=True, seed=seed)
+          for seed, (dtype, B, H, T) in enumerate([("bf16", 16, 2048, 5), ("bf16", 17, 1120, 4), ("f32", 16, 544, 5),
+                                                   ("f32", 9, 1024, 5), ("f32", 160, 1024, 4), ("f32", 193, 736, 4),
+                                                   ("f32", 225, 576, 4)], start=371)]
 
 
 @pytest.mark.parametrize("w", CASES, ids=[w.name for w in CASES])
