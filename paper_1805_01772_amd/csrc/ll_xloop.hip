@@ -140,8 +140,10 @@ __device__ __forceinline__ char* ring_tile(const XLoopArgs& a, int slot, int grp
 // stack slot k (rows k * slot_rows + compact row), the guard (1 = the row
 // pondered) and the state h^{k+1} (into HI); per (step, row tile) the inner
 // trip count (ntrip).  The exchange counts ponder iterations, not steps.
+// FIVE: the stack is known to be resident with five values a unit (a layer of
+// the two-layer wavefront).
 template <typename T, int NCT, int KSW, int KSR, int MRT_MAX, bool TOP, int G = 4, bool SKIP = false,
-          bool ACT = false>
+          bool ACT = false, bool FIVE = false>
 __device__ __forceinline__ void xfwd_body(const XLoopArgs& a, int grp, int rank, uint4* lds) {
   constexpr bool PRED = SKIP || ACT;   // the extra predicate column of the recurrent product
   constexpr int KPC = Op<T>::kPerChunk;
@@ -462,7 +464,11 @@ __device__ __forceinline__ void xfwd_body(const XLoopArgs& a, int grp, int rank,
         HH[cr * H + ju] = Op<T>::from_f32(hn);
         if (a.stack) {
           const long sr = (long)(srow0 + t) * B + r;
-          if constexpr (G == 4 || G == 3) {
+          if constexpr (FIVE) {
+            float* srow = a.stack + ((long)t * B + r) * a.sld;
+            *reinterpret_cast<float4*>(srow + 4 * ju) = make_float4(ig, fg, gg, og);
+            srow[a.sld / 5 * 4 + ju] = cn;
+          } else if constexpr (G == 4 || G == 3) {
             // the unit's four gate values side by side (stack row: 4H gate
             // values unit by unit): one 16-byte store
             if (a.sgates) *reinterpret_cast<float4*>(a.stack + sr * a.sld + 4 * ju) = make_float4(ig, fg, gg, og);
@@ -535,10 +541,15 @@ __global__ __launch_bounds__(XNT, 1) void xfwd2_kernel(XLoopArgs a0, XLoopArgs a
     }
     return;
   }
+  // Stack rows by their one layout hold fewer scalar registers across the
+  // loop than by the general one (inference of 100 steps: bf16 H = 512 B = 64
+  // 297 -> 287 us, f32 H = 64 B = 128 237 -> 223); float32's wider layers are
+  // faster with the general one (H = 256 B = 64 407 and 396).
+  constexpr bool FIVE = sizeof(T) == 2 || KSWB == 1;
   if (rank < a0.P)
-    xfwd_body<T, NCT, KSWB, KSRB, MRT_MAX, false>(a0, grp, rank, lds);
+    xfwd_body<T, NCT, KSWB, KSRB, MRT_MAX, false, 4, false, false, FIVE>(a0, grp, rank, lds);
   else if (rank < a0.P + a1.P)
-    xfwd_body<T, NCT, KSWT, KSRT, MRT_MAX, true>(a1, grp, rank - a0.P, lds);
+    xfwd_body<T, NCT, KSWT, KSRT, MRT_MAX, true, 4, false, false, FIVE>(a1, grp, rank - a0.P, lds);
 }
 
 // ---------------------------------------------------------------------------
