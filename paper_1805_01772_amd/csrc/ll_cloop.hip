@@ -21,12 +21,13 @@
 // of the group, like the KG slices (gradient), and the waves of a SIMD hide
 // each other's waits.  Measured: the forward loop with a reduction split over
 // KG = 2 / 4 work-groups and their partial products in the L2 took, per step,
-// bf16 H = 2048 18.0 us (B = 64), 23.9 (128), 32.1 (256), H = 1536 15.7 (64),
-// 19.1 (128), f32 H = 640 16.4 (64), 15.2 (128); with the whole reduction per
-// work-group 11.7, 14.3, 31.3, 10.0, 11.3, 10.4, 11.8.  Above 128 rows the
-// 1 MB that every work-group then streams evens the two out (B = 160 to 192
-// of bf16 H = 2048 and 256 of f32 H = 1024 are 4-7 % slower than split, the
-// narrower widths 4-16 % faster).
+// bf16 H = 2048 18.0 us (B = 64), 23.9 (128), H = 1536 15.7 (64), 19.1 (128),
+// f32 H = 640 16.4 (64), 15.2 (128); with the whole reduction per work-group
+// 11.7, 14.3, 10.0, 11.3, 10.4, 11.8.  Above 128 rows, where every work-group
+// then streams up to 1 MB a step, the two are closer (inference of 40 steps,
+// I = 512, split and whole: bf16 H = 2048 B = 160 913 and 846 us, 192 994 and
+// 919, 256 1215 and 1157, H = 1536 B = 256 967 and 771; f32 H = 1024 B = 160
+// 1192 and 1050, 224 1342 and 1384, 256 1444 and 1432).
 //
 // One step of a forward wave:
 //   wait for the producers of its k-steps of h_{t-1} (the next step's input
@@ -418,7 +419,7 @@ __device__ __forceinline__ void cfwd_product(__amdgpu_buffer_rsrc_t rs, const ui
 template <typename T, int KW, int RTL, int NW>
 __global__ __launch_bounds__(64 * NW, 1) void cfwd_kernel(CLoopArgs a) {
   using S = CFwd<T, KW, RTL, NW>;
-  constexpr int KPC = S::KPC, RW = S::RW, NT = S::NT, RT = S::RT, NCF = S::NCF;
+  constexpr int KPC = S::KPC, RW = S::RW, NT = S::NT, RT = S::RT, NCF = S::NCF, U = cfwd_unroll<T, KW, NW>();
   extern __shared__ uint4 lds[];
   const int H = a.H, B = a.B, RGN = a.RGN;
   const int wg = blockIdx.x, jb = wg * KPC;
@@ -448,7 +449,10 @@ __global__ __launch_bounds__(64 * NW, 1) void cfwd_kernel(CLoopArgs a) {
   __syncthreads();
   // (sixteen waves: neighbours share a row group, so that five or six groups
   // spread over the four SIMDs)
-  const int rg = NW == 16 ? wave / KW : wave % RW, kw = NW == 16 ? wave % KW : wave / RW;
+  const int rg = NW == 16 ? wave / KW : wave % RW;
+  int kw = NW == 16 ? wave % KW : wave / RW;
+  // (told that kw is 0 or 1, the compiler indexes acc with it, in scratch)
+  if constexpr (NW == 16) asm("" : "+s"(kw));
   auto wave_of = [&](int k) { return NW == 16 ? rg * KW + k : k * RW + rg; };
   if (rg >= RGN) return;
   // cells: row tiles rt0 .. rt0 + RT - 1, row l16 of each, units j .. j + NT - 1
@@ -507,10 +511,24 @@ __global__ __launch_bounds__(64 * NW, 1) void cfwd_kernel(CLoopArgs a) {
       for (int n = 0; n < NT; ++n) zc[e][n] = zx[e][n];
     load_zx(A_n, off_t + A_t);
     if (t > 0 && nks > 0) wait_quads(a, rfl, nfl, (unsigned)(t + 1));
+    const __amdgpu_buffer_rsrc_t rs =
+        make_rsrc(reinterpret_cast<char*>(a.ring) + (((long)((t + 1) & 1) * RGN + rg) * KS + ks0) * 2048,
+                  (unsigned)nks << 11);
     f32x4 acc[NT][RTL];
-    cfwd_product<T, NT, RTL, cfwd_unroll<T, KW, NW>()>(make_rsrc(reinterpret_cast<char*>(a.ring) + (((long)((t + 1) & 1) * RGN + rg) * KS + ks0) * 2048,
-                                  (unsigned)nks << 11),
-                        w, KSP / cfwd_unroll<T, KW, NW>(), wg >> 3, acc);
+    // sixteen waves are bound by the matrix cores enough to leave a row tile
+    // out once its rows have finished (or for a last row group of one tile);
+    // eight lose more by the second loop (bf16 H = 2048 B = 40 422 -> 498 us)
+    if (NW == 16 && nr <= 16) {
+      f32x4 first[NT][1];
+      cfwd_product<T, NT, 1, U>(rs, w, KSP / U, wg >> 3, first);
+#pragma unroll
+      for (int n = 0; n < NT; ++n) {
+        acc[n][0] = first[n][0];
+        acc[n][RTL - 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    } else {
+      cfwd_product<T, NT, RTL, U>(rs, w, KSP / U, wg >> 3, acc);
+    }
     if constexpr (KW > 1) {
       // the shares meet in LDS: each stores its product of the row tiles that
       // are not its own (once their cell waves have read step t-1's), wave
@@ -994,8 +1012,9 @@ CKernels c_make(int H, int rgn) {
 // 330 -> 278; f32 H = 1024 389 -> 327, H = 544 338 -> 275).  float32's five
 // or six row groups: eight waves of a group each would put two on one SIMD
 // and one on each of the others, at 6.8 us of matrix work a step (H = 1024);
-// sixteen, two to a group, spread it (H = 1024 B = 160 1221 -> 1163 us, 192
-// 1307 -> 1229; seven or eight groups are even either way: 224 1410 -> 1495).
+// sixteen, two to a group, spread it (H = 1024 B = 144 1174 -> 994 us, 160
+// 1221 -> 1050, 192 1307 -> 1084; seven or eight groups are even either way:
+// 224 1410 -> 1495).
 // bfloat16's products are a quarter as long and its weights and shares of two
 // exceed the LDS.
 template <typename T>

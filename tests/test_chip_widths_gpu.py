@@ -36,7 +36,7 @@ CASES += [W(f"chipw_{dtype}_b{B}_i8_h{H}_t{T}", B=B, I=8, H=H, T_max=T, dtype=dt
             random_state=True, seed=seed)
           for seed, (dtype, B, H, T) in enumerate([("bf16", 16, 2048, 5), ("bf16", 17, 1120, 4), ("f32", 16, 544, 5),
                                                    ("f32", 9, 1024, 5), ("f32", 160, 1024, 4), ("f32", 193, 736, 4),
-                                                   ("f32", 225, 576, 4)], start=371)]
+                                                   ("f32", 225, 576, 4), ("f32", 129, 1024, 6)], start=371)]
 
 
 @pytest.mark.parametrize("w", CASES, ids=[w.name for w in CASES])
