@@ -229,8 +229,9 @@ ll_status ll_plan_stack_bytes(const ll_plan* plan, int64_t* device_bytes,
 #define LL_LOOPS_CHIP 2   /* weights split over all XCDs, per-tile flags      */
 
 /* Launch geometry the plan chose for the recurrent loops (for reports):
- * work-groups per loop launch, hidden units per work-group (the cell units
- * of a work-group in the chip-wide form), row groups (independent
+ * work-groups per loop launch (chip-wide form: of the gradient loop; the
+ * forward loop launches H / units_per_workgroup), hidden units per work-group
+ * (the cell units of a work-group in the chip-wide form), row groups (independent
  * recurrences), the loop form (LL_LOOPS_*: XCD-local where one XCD holds the
  * recurrent weights, chip-wide where it cannot (bf16 H <= 2048, f32
  * H <= 1024, B <= 256), grid-barrier otherwise), and whether a two-layer plan runs its layers
@@ -243,9 +244,9 @@ ll_status ll_plan_stack_bytes(const ll_plan* plan, int64_t* device_bytes,
  * 2H / units_per_workgroup <= 32; its results equal the layer-by-layer
  * ones up to the order of floating-point sums.  dw_in_place: bit l set when
  * layer l's dW products read x (or the layer below's h history), the h history
- * and dz in place, row by row (bfloat16 layers whose reduction is short enough
- * for that to be faster and whose operands stay below 2^31 bytes); clear when
- * they read transposed copies. */
+ * and dz in place, row by row (layers whose operands stay below 2^31 bytes:
+ * every float32 one, and the bfloat16 ones whose reduction is short enough for
+ * that to be faster); clear when they read transposed copies. */
 ll_status ll_plan_geometry(const ll_plan* plan, int32_t* loop_workgroups,
                            int32_t* units_per_workgroup,
                            int32_t* row_groups, int32_t* loop_form,

@@ -79,7 +79,9 @@ __device__ __forceinline__ float tanhf_(float u) {
 }
 
 // c_t = f c_{t-1} + i g with the rounding pinned (one product rounded, one
-// fused), so that every kernel that computes it gets the same bits.
+// fused), so that a swapped chunk's rebuilt c has the bits of the XCD-local
+// forward loop's (the grid-barrier loops, which swap nothing, leave the
+// rounding to the compiler).
 __device__ __forceinline__ float lstm_c(float i, float f, float g, float c) {
   return __builtin_fmaf(f, c, __fmul_rn(i, g));
 }

@@ -247,7 +247,7 @@ struct ll_plan {
   // XCD-local LSTM gradient loops: W_h of each layer in the unit-major
   // reduction order ([H, 4H], operand type)
   void* Wum[2] = {nullptr, nullptr};
-  // bf16 dW from the row-major operands: h history row of each compact row's
+  // dW from the row-major operands: h history row of each compact row's
   // h_{t-1} (h0 rows after the history), and the split-K of each product
   int* prevc = nullptr;
   int tn_splits[2][3] = {{1, 1, 1}, {1, 1, 1}};
@@ -542,9 +542,9 @@ ll_status plan_configure(ll_plan* p, const ll_desc* desc, int device, const hipD
   // work-group, f32: 16).  The exchange moves whole k-step blocks, so any
   // H % 32 fits; a bf16 width that is an odd number of 32 units (rows not
   // 128-byte aligned) takes them for the LSTM body with its stack resident
-  // (training step of 60 steps, grid-barrier loops before and here: H = 96,
-  // B = 50 0.81 and 0.31 ms; H = 992, B = 512 7.15 and 1.88 ms); the other
-  // bodies and memory policies refuse it.
+  // (training step of 60 steps, I = 256, grid-barrier loops before and here:
+  // H = 96, B = 50 0.81 and 0.30 ms; H = 992, B = 512 9.02 and 2.26 ms); the
+  // other bodies and memory policies refuse it.
   const char* loops_env = getenv("LSTMLOOP_LOOPS");
   const bool allow = !(loops_env && strcmp(loops_env, "grid") == 0);
   {
