@@ -305,11 +305,13 @@ __global__ __launch_bounds__(256) void permute_um_kernel(const T* __restrict__ W
 // It replaces a fifth of the swapped bytes: f32 H = 512, B = 64, T = 2000
 // through a ring of four 32-step chunks, 55.6 -> 46.9 ms a training step.
 // c_in: c entering the chunk, in the caller's row order (perm) or, without
-// perm, in length order; it may be c's own first row (each thread reads its
-// element before it writes there).
-__global__ __launch_bounds__(256) void rebuild_c_kernel(const float* __restrict__ gates, const float* c_in,
+// perm, in length order; then it lies in pinned host memory and is read from
+// there (one 4-byte read per thread beside 32 x 16 from HBM; as a copy of its
+// own each way it took 12 us of the copy streams, 48.5 ms a step).
+__global__ __launch_bounds__(256) void rebuild_c_kernel(const float* __restrict__ gates,
+                                                        const float* __restrict__ c_in,
                                                         const int* __restrict__ perm, const int* __restrict__ active,
-                                                        int B, int H, int t0, int t1, float* c) {
+                                                        int B, int H, int t0, int t1, float* __restrict__ c) {
   const long i = blockIdx.x * 256L + threadIdx.x;
   if (i >= (long)B * H) return;
   const int r = (int)(i / H), u = (int)(i - (long)r * H);
@@ -321,6 +323,20 @@ __global__ __launch_bounds__(256) void rebuild_c_kernel(const float* __restrict_
     v = lstm_c(g.x, g.y, g.z, v);
     c[row * H + u] = v;
   }
+}
+
+// n floats (a multiple of 4, 16-byte aligned) to pinned host memory.
+__global__ __launch_bounds__(256) void copy_row_kernel(const float4* __restrict__ src, float4* __restrict__ dst,
+                                                       int n4) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n4) dst[i] = src[i];
+}
+
+hipError_t launch_copy_row(const float* src, float* dst, long n, hipStream_t s) {
+  const int n4 = (int)(n / 4);
+  hipLaunchKernelGGL(copy_row_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s,
+                     reinterpret_cast<const float4*>(src), reinterpret_cast<float4*>(dst), n4);
+  return hipGetLastError();
 }
 
 hipError_t launch_rebuild_c(const float* gates, const float* c_in, const int* perm, const int* active, int B, int H,

@@ -431,8 +431,10 @@ hipError_t launch_zero_u32(unsigned* p, int n, hipStream_t s);
 // c of steps [t0, t1) rebuilt from the gates (rows (t - t0) B + r of `gates`
 // [.., 4H], unit u's i, f, g, o at 4u) and the entering state c_in [B, H]
 // (NULL: zeros; in the caller's row order if perm is given, else in length
-// order, and then possibly c's first row), into rows (t - t0) B + r of
-// c [.., H]: the same operations as the forward loop's, so the same bits.
+// order, as launch_copy_row took it from c's last row of the chunk before to
+// pinned host memory), into rows (t - t0) B + r of c [.., H]: the same
+// operations as the forward loop's, so the same bits.
+hipError_t launch_copy_row(const float* src, float* dst, long n, hipStream_t s);
 hipError_t launch_rebuild_c(const float* gates, const float* c_in, const int* perm, const int* active, int B, int H,
                             int t0, int t1, float* c, hipStream_t s);
 

@@ -1350,20 +1350,19 @@ ll_status enqueue_fwd(ll_plan* p, hipStream_t s, const void* x, const int32_t* s
         LL_HIP(chained_loop_launch(p->device, s, [&] { return ll::x_launch(p->xk.fwd, xa, 256, p->xk.lds_fwd, s); }));
         tend(p, s, LL_STAGE_FWD_LOOP, ev);
         if (p->spill && save && k < nch - p->nslots) {   // evicted later: swap it out on the copy stream
+          // the whole slot, or the gates and then c of the chunk's last step,
+          // from which the next chunk's c is rebuilt (rows in length order;
+          // those that ended in this chunk are not read)
+          const long row_floats = (long)B * H, moved = p->c_rebuilt ? C * 4 * row_floats : p->slot_floats;
+          float* const host = p->host_stack[l] + (long)k * p->slot_floats;
+          if (p->c_rebuilt)
+            LL_HIP(ll::launch_copy_row(xa.cstk + (slot * (long)C + C - 1) * row_floats, host + moved, row_floats, s));
           LL_HIP(hipEventRecord(p->ev_compute, s));
           // (two copy streams: the next chunk's copy is queued while this one runs)
           hipStream_t cs = (k & 1) ? p->cstream2 : p->cstream;
           LL_HIP(hipStreamWaitEvent(cs, p->ev_compute, 0));
-          // the whole slot, or the gates and then c of the chunk's last step:
-          // the next chunk's c is rebuilt from it (rows in length order; those
-          // that ended in this chunk are not read)
-          const long row_floats = (long)B * H, moved = p->c_rebuilt ? C * 4 * row_floats : p->slot_floats;
-          float* const host = p->host_stack[l] + (long)k * p->slot_floats;
           LL_HIP(copy_on_dma_engine(host, p->stack[l] + slot * moved, sizeof(float) * moved, hipMemcpyDeviceToHost,
                                     cs));
-          if (p->c_rebuilt)
-            LL_HIP(copy_on_dma_engine(host + moved, xa.cstk + (slot * (long)C + C - 1) * row_floats,
-                                      sizeof(float) * row_floats, hipMemcpyDeviceToHost, cs));
           LL_HIP(hipEventRecord(p->ev_d2h[l * p->nslots + slot], cs));
         }
         hin = p->carry;
@@ -2047,9 +2046,9 @@ ll_status enqueue_bwd(ll_plan* p, hipStream_t s, const float* dy, const float* d
         LL_HIP(hipStreamWaitEvent(s, p->ev_h2d[l * R + j % R], 0));
         if (!p->c_rebuilt) return LL_OK;
         const long rows = (long)C * B;
-        float* const c = xa.cstk + (j % R) * rows * H;
-        LL_HIP(ll::launch_rebuild_c(p->stack[l] + (j % R) * rows * 4 * H, j > 0 ? c : xa.c0,
-                                    j > 0 ? nullptr : p->perm, p->active, B, H, j * C, (j + 1) * C, c, s));
+        const float* cin = j > 0 ? p->host_stack[l] + (long)(j - 1) * p->slot_floats + rows * 4 * H : xa.c0;
+        LL_HIP(ll::launch_rebuild_c(p->stack[l] + (j % R) * rows * 4 * H, cin, j > 0 ? nullptr : p->perm, p->active,
+                                    B, H, j * C, (j + 1) * C, xa.cstk + (j % R) * rows * H, s));
         return LL_OK;
       };
       for (int k = nch - 1; k >= 0; --k) {
@@ -2077,14 +2076,9 @@ ll_status enqueue_bwd(ll_plan* p, hipStream_t s, const float* dy, const float* d
           LL_HIP(hipEventRecord(p->ev_compute, s));
           hipStream_t cs = (j & 1) ? p->cstream2 : p->cstream;
           LL_HIP(hipStreamWaitEvent(cs, p->ev_compute, 0));
-          // (c entering the chunk waits in the chunk's first row of c)
-          const long row_floats = (long)B * H, moved = p->c_rebuilt ? C * 4 * row_floats : p->slot_floats;
-          float* const host = p->host_stack[l] + (long)j * p->slot_floats;
-          LL_HIP(copy_on_dma_engine(p->stack[l] + (j % R) * moved, host, sizeof(float) * moved,
-                                    hipMemcpyHostToDevice, cs));
-          if (p->c_rebuilt && j > 0)
-            LL_HIP(copy_on_dma_engine(xa.cstk + (j % R) * C * row_floats, host - p->slot_floats + moved,
-                                      sizeof(float) * row_floats, hipMemcpyHostToDevice, cs));
+          const long moved = p->c_rebuilt ? (long)C * B * 4 * H : p->slot_floats;
+          LL_HIP(copy_on_dma_engine(p->stack[l] + (j % R) * moved, p->host_stack[l] + (long)j * p->slot_floats,
+                                    sizeof(float) * moved, hipMemcpyHostToDevice, cs));
           LL_HIP(hipEventRecord(p->ev_h2d[l * R + j % R], cs));
         }
       }
