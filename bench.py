@@ -160,6 +160,17 @@ def recorded_traffic(kernel, workload):
     return float(ent["bytes_per_launch"])
 
 
+def swapped_bytes(host_bytes, slot_bytes, B, H):
+    """(bytes a copy moves, bytes that cross the host link one way a pass) of a
+    swapped stack with host_bytes of chunk slots in host memory: whole slots
+    below 3 MiB, else their gates and, moved by kernels, c of the last step
+    (see the spill policy in include/lstmloop.h)."""
+    if slot_bytes < 3 << 20:
+        return slot_bytes, host_bytes
+    copy = slot_bytes * 4 // 5
+    return copy, host_bytes // slot_bytes * (copy + B * H * 4)
+
+
 def pinned_copy_peak(nbytes, streams=1, reps=5):
     """Host-link rate of plain copies between pinned host memory and device
     memory: GB/s for device-to-host and host-to-device, each direction alone,
@@ -273,20 +284,21 @@ def main():
     if w.spill:
         res_ms = timed({}, False)[0]
         nch = -(-w.T_max // C)
-        moved = 2 * sbytes[1]   # the chunks evicted from the device ring go out once and come back once
+        slot_bytes = C * w.B * 5 * w.H * 4
+        copy_bytes, one_way = swapped_bytes(sbytes[1], slot_bytes, w.B, w.H)
+        moved = 2 * one_way   # the chunks evicted from the device ring go out once and come back once
         # the alternative to swapping: push c_t only, recompute each chunk's
         # gates in the gradient pass (two products over the chunk's rows)
         rc = timed({"recompute": 1, "spill_chunk_steps": C}, False)
-        slot_bytes = C * w.B * 5 * w.H * 4
-        peak1 = pinned_copy_peak(slot_bytes, 1)
-        peak2 = pinned_copy_peak(slot_bytes, 2)
+        peak1 = pinned_copy_peak(copy_bytes, 1)
+        peak2 = pinned_copy_peak(copy_bytes, 2)
         link = moved / (gpu_ms / args.steps / 1e3) / 1e9
         spill = {"chunk_steps": C, "ring_slots": 4, "device_stack_bytes": sbytes[0],
                  "host_stack_bytes": sbytes[1], "ms_per_step_resident": res_ms / args.steps,
                  "ms_per_step_recompute": rc[0] / args.steps, "device_stack_bytes_recompute": rc[4][0],
                  "overlap_efficiency": (res_ms / args.steps) / (gpu_ms / args.steps),
                  "host_link_GBps": link,
-                 "pinned_copy_peak_GBps": {"chunk_bytes": slot_bytes, "one_stream": peak1,
+                 "pinned_copy_peak_GBps": {"chunk_bytes": copy_bytes, "one_stream": peak1,
                                            "two_streams": peak2},
                  "host_link_fraction_of_peak": link / max(peak1["d2h"], peak1["h2d"], 1e-9),
                  "seconds_at_peak": moved / 2 / peak1["d2h"] / 1e9 + moved / 2 / peak1["h2d"] / 1e9}

@@ -47,3 +47,13 @@ def test_committed_record_names_existing_sources(kernel):
     for e in ents:
         for rel in e["sources"]:
             assert os.path.exists(os.path.join(ROOT, rel)), rel
+
+
+def test_swapped_bytes_counts_what_crosses_the_host_link():
+    # 64 x 512, chunks of 32 steps: 59 slots, four of the five values a unit and one row of c
+    slot = 32 * 64 * 5 * 512 * 4
+    copy, one_way = bench.swapped_bytes(59 * slot, slot, 64, 512)
+    assert copy == 32 * 64 * 4 * 512 * 4 and one_way == 59 * (copy + 64 * 512 * 4)
+    # chunks below 3 MiB cross whole
+    slot = 4 * 64 * 5 * 512 * 4
+    assert bench.swapped_bytes(7 * slot, slot, 64, 512) == (slot, 7 * slot)
