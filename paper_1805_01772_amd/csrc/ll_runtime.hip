@@ -1350,13 +1350,11 @@ ll_status enqueue_fwd(ll_plan* p, hipStream_t s, const void* x, const int32_t* s
         LL_HIP(chained_loop_launch(p->device, s, [&] { return ll::x_launch(p->xk.fwd, xa, 256, p->xk.lds_fwd, s); }));
         tend(p, s, LL_STAGE_FWD_LOOP, ev);
         if (p->spill && save && k < nch - p->nslots) {   // evicted later: swap it out on the copy stream
-          // the whole slot, or the gates and then c of the chunk's last step,
-          // from which the next chunk's c is rebuilt (rows in length order;
-          // those that ended in this chunk are not read)
+          // the whole slot, or the gates and, behind them, c of the chunk's last
+          // step, from which the next chunk's c is rebuilt (rows in length
+          // order; those that ended in this chunk are not read)
           const long row_floats = (long)B * H, moved = p->c_rebuilt ? C * 4 * row_floats : p->slot_floats;
           float* const host = p->host_stack[l] + (long)k * p->slot_floats;
-          if (p->c_rebuilt)
-            LL_HIP(ll::launch_copy_row(xa.cstk + (slot * (long)C + C - 1) * row_floats, host + moved, row_floats, s));
           LL_HIP(hipEventRecord(p->ev_compute, s));
           // (two copy streams: the next chunk's copy is queued while this one runs)
           hipStream_t cs = (k & 1) ? p->cstream2 : p->cstream;
@@ -1364,6 +1362,8 @@ ll_status enqueue_fwd(ll_plan* p, hipStream_t s, const void* x, const int32_t* s
           LL_HIP(copy_on_dma_engine(host, p->stack[l] + slot * moved, sizeof(float) * moved, hipMemcpyDeviceToHost,
                                     cs));
           LL_HIP(hipEventRecord(p->ev_d2h[l * p->nslots + slot], cs));
+          if (p->c_rebuilt)   // (on this stream: done before the next launch)
+            LL_HIP(ll::launch_copy_row(xa.cstk + (slot * (long)C + C - 1) * row_floats, host + moved, row_floats, s));
         }
         hin = p->carry;
         cin = p->carry + (long)B * H;
